@@ -14,7 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmmx.so")
 SOURCES = ["kernels.hip", "mid_f32.hip", "mid_f64.hip", "passes_f32.hip", "passes_f64.hip",
-           "local_ext_f32.hip", "local_ext_f64.hip", "api.hip", "serve.hip"]
+           "plane_f32.hip", "plane_f64.hip", "local_ext_f32.hip", "local_ext_f64.hip", "api.hip", "serve.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -56,6 +56,7 @@ struct Plan {
     long S1n;      // complex values in S1 = 3 * nz * ny * Hxp
     long S2n;      // complex values in S2 = 3 * nz * Py * Hxp
     long Kn;       // reals per spectral-tensor component (Pz/2+1)(Py/2+1) Hxp
+    bool plane = false;  // the y and z passes run as one kernel (plane.h); Khat in its layout
     int Lmax;      // twiddle table length = max(P)
     // material
     int prec;      // MM_FP32 / MM_FP64
@@ -84,9 +85,11 @@ struct Plan {
     hipStream_t stream;
     int ncu = 256;  // compute units of the device (persistent launches)
     // device buffers (element type = plan precision unless noted)
-    void *Khat = nullptr;     // [6][Pz/2+1][Py/2+1][Hxp] real, scaled by 1/(Px Py Pz)
-    void *S1 = nullptr;       // [3][nz][ny][Hxp] complex
-    void *S2 = nullptr;       // [3][nz][Py][Hxp] complex (aliases S1 when Py == 1)
+    void *Khat = nullptr;     // [6][Pz/2+1][Py/2+1][Hxp] real, scaled by 1/(Px Py Pz); plane:
+                              // [Px/2+1][ky parity][6][Pz/2+1][ky/2] in the same buffer
+    void *S1 = nullptr;       // [3][nz][ny][Hxp] complex (plane: scratch of k_plane)
+    void *S2 = nullptr;       // [3][nz][Py][Hxp] complex (aliases S1 when Py == 1); plane: the x
+                              // spectrum [Px/2][3][nz][ny rounded up to even]
     void *tw = nullptr;       // Lmax complex roots exp(-2 pi i n / Lmax)
     void *Ms_cell = nullptr;  // N reals, or null
     void *A_cell = nullptr;   // N reals (per-cell exchange constant), or null
@@ -141,6 +144,9 @@ hipError_t prof_flush(Plan &p);
 
 // Thread-local error message (mm_last_error).
 void set_error(const std::string &msg);
+
+// Whether the one-kernel y/z passes cover these padded extents.
+bool plane_shape(int prec, int Px, int Py, int Pz);
 
 // Device pipeline, instantiated for float and double in kernels.hip.
 template <typename T>

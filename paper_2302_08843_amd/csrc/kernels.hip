@@ -18,12 +18,14 @@
 //       (Sec. 3, Eq. llg) and the torque maximum used by relaxation.
 //
 // With a single layer (Pz = 1) F2/F3/I2 collapse into one kernel (y forward,
-// product, y inverse).  The 1/(Px Py Pz) of the inverse transform is folded
+// product, y inverse), and on grids whose y-z plane fits a compute unit too
+// (plane.h), on a spectrum laid out for it.  The 1/(Px Py Pz) of the inverse transform is folded
 // into the resident spectral kernel.  No MFMA: FFTs and stencils are not dense
 // contractions; everything here is VALU + LDS, bounded by HBM traffic.
 #include <cstring>
 
 #include "passes.h"
+#include "plane.h"
 
 namespace mmx {
 
@@ -587,6 +589,7 @@ struct AdjParams {
     long s1_comp;
     int Hxp;
     int with_demag, with_exch, with_anis;
+    int tr;       // transposed spectrum (plane plans)
     double Ms;
     double exch;  // 2 A / mu0
     double idx2, idy2, idz2;
@@ -610,7 +613,12 @@ __global__ __launch_bounds__((XC2R<T, M>::kRows * 3 * XC2R<T, M>::kT)) void k_ad
     const int k = MMX_X1_KFAST ? (int)(lb % P.nz) : (int)(lb / njt);
     const int j0 = (MMX_X1_KFAST ? (int)(lb / P.nz) : (int)(lb % njt)) * kRows;
     const int nx = P.nx, ny = P.ny;
-    if (P.with_demag) x_c2r_rows<T, M>(S1, lds, k, j0, ny, P.s1_comp, P.Hxp, tw, Lmax);
+    if (P.with_demag) {
+        if (P.tr)
+            x_c2r_rows<T, M, true>(S1, lds, k, j0, ny, P.s1_comp, P.Hxp, tw, Lmax, P.nz);
+        else
+            x_c2r_rows<T, M>(S1, lds, k, j0, ny, P.s1_comp, P.Hxp, tw, Lmax);
+    }
     const long N = P.N;
     const T exch = (T)P.exch, anis = (T)P.anis;
     const T ix2 = (T)P.idx2, iy2 = (T)P.idy2, iz2 = (T)P.idz2;
@@ -748,7 +756,7 @@ static hipError_t launch_adj_M(const Plan& p, const T* m, const T* z, const T* g
     const int njt = (p.n[1] + G::kRows - 1) / G::kRows;
     const long nblocks = (long)njt * p.n[2];
     k_adj_local<T, M, PC><<<xcd_grid(nblocks), G::kRows * 3 * G::kT, 0, p.stream>>>(
-        (const cx<T>*)p.S1, m, z, g, (const T*)p.Ms_cell, P, nu, gms, njt, nblocks,
+        (const cx<T>*)(p.plane ? p.S2 : p.S1), m, z, g, (const T*)p.Ms_cell, P, nu, gms, njt, nblocks,
         (const cx<T>*)p.tw, p.Lmax);
     return hipGetLastError();
 }
@@ -842,6 +850,60 @@ __global__ void k_fold(T* __restrict__ Khat, const cx<double>* __restrict__ C, i
         hipError_t e__ = (x);             \
         if (e__ != hipSuccess) return e__; \
     } while (0)
+
+// The same in the plane layout: column kx, parity q of ky, component s, kz,
+// ky / 2 (plane_koff).
+__host__ __device__ inline long plane_index(int s, int kx, int ky, int kz, int Py, int Pz)
+{
+    const int YP = Py / 2, hz = Pz / 2 + 1, q = ky & 1;
+    return (long)kx * 6 * hz * (YP + 1) + plane_koff(q, YP, hz) +
+           ((long)s * hz + kz) * plane_kn(q, YP) + (ky >> 1);
+}
+template <typename T>
+__global__ void k_fold_plane(T* __restrict__ Khat, const cx<double>* __restrict__ C, int s, int Hx,
+                             int Hxp, int Py, int Pz, double scale)
+{
+    const int hy = Py / 2 + 1, hz = Pz / 2 + 1;
+    const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= (long)hz * hy * Hx) return;
+    const int kx = (int)(q % Hx), ky = (int)((q / Hx) % hy), kz = (int)(q / ((long)Hx * hy));
+    Khat[plane_index(s, kx, ky, kz, Py, Pz)] = (T)(C[((long)kz * Py + ky) * Hxp + kx].x * scale);
+}
+
+// Plane kernel or the three passes.  It needs enough columns (Px / 2 blocks):
+// a plane beyond half a compute unit's LDS leaves it to one block, which only
+// pays when the blocks cover the chip in FP64 (100x500x3: 69 us a field
+// against the passes' 55, 512x512x4: 151 against 171) and, one q after the
+// other, in FP32 (102x163x10: 71 against 57, 256x256x16: 91 against 107);
+// with both q at once in FP32 from 32 columns on (8x512x4: 34 against 32,
+// 31x221x3: 25 against 34).  Many columns of very few rows or of deep stacks
+// make many short blocks (512x5x3: 22 against 21, 512x20x20: 56 against 54).
+template <typename G>
+static bool plane_pays(int prec, int Px, int Py, int Pz)
+{
+    if (Px < 4 || (Px >= 1024 && (Py <= 16 || Pz >= 64))) return false;
+    if (prec == MM_FP64 && G::kBytes > 80 * 1024) return Px >= 512;
+    if (G::kNT == G::kNTQ) return Px >= 512;
+    return G::kBytes <= 80 * 1024 || Px >= 64;
+}
+
+bool plane_shape(int prec, int Px, int Py, int Pz)
+{
+#define MMX_PLANE_HAS(T, YP, EY, PZ, LZ, NQ, NTQ) \
+    if (Py == 2 * YP && Pz == PZ)                 \
+        return plane_pays<PlaneG<T, YP, EY, PZ, LZ, NQ, NTQ>>(prec, Px, Py, Pz);
+#define MMX_PLANE_HAS32(YP, EY, PZ, LZ, NQ, NTQ) MMX_PLANE_HAS(float, YP, EY, PZ, LZ, NQ, NTQ)
+#define MMX_PLANE_HAS64(YP, EY, PZ, LZ, NQ, NTQ) MMX_PLANE_HAS(double, YP, EY, PZ, LZ, NQ, NTQ)
+    if (prec == MM_FP32) {
+        MMX_PLANE_F32(MMX_PLANE_HAS32)
+    } else {
+        MMX_PLANE_F64(MMX_PLANE_HAS64)
+    }
+#undef MMX_PLANE_HAS
+#undef MMX_PLANE_HAS32
+#undef MMX_PLANE_HAS64
+    return false;
+}
 
 static long blocks_for(long n, int bs) { return (n + bs - 1) / bs; }
 
@@ -1134,8 +1196,12 @@ hipError_t build_tensor(Plan& p)
             MMX_TRY((launch_strided<double, -1>(q, Pz, C, C, Pz, Pz, (long)Py * p.Hxp,
                                                 (long)Py * p.Hxp, p.Hx, 1, 0, 0, Py, p.Hxp,
                                                 p.Hxp)));
-        k_fold<T><<<blocks_for(p.Kn, 256), 256, 0, p.stream>>>(
-            (T*)p.Khat + s * p.Kn, C, p.Hx, p.Hxp, Py, Pz, 1.0 / (double)PN);
+        if (p.plane)
+            k_fold_plane<T><<<blocks_for(p.Kn, 256), 256, 0, p.stream>>>(
+                (T*)p.Khat, C, s, p.Hx, p.Hxp, Py, Pz, 1.0 / (double)PN);
+        else
+            k_fold<T><<<blocks_for(p.Kn, 256), 256, 0, p.stream>>>(
+                (T*)p.Khat + s * p.Kn, C, p.Hx, p.Hxp, Py, Pz, 1.0 / (double)PN);
         MMX_TRY(hipGetLastError());
     }
     return hipStreamSynchronize(p.stream);
@@ -1151,11 +1217,28 @@ __global__ void k_to_double(const T* in, double* out, long n, int Hx, int Hxp)
     out[q] = (double)in[row * Hxp + kx];
 }
 
+// The same from the plane layout.
+template <typename T>
+__global__ void k_plane_to_double(const T* in, double* out, int s, int Hx, int Py, int Pz)
+{
+    const int hy = Py / 2 + 1, hz = Pz / 2 + 1;
+    const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= (long)hz * hy * Hx) return;
+    const int kx = (int)(q % Hx), ky = (int)((q / Hx) % hy), kz = (int)(q / ((long)Hx * hy));
+    out[q] = (double)in[plane_index(s, kx, ky, kz, Py, Pz)];
+}
+
 template <typename T>
 hipError_t debug_spectrum(Plan& p, int s, double* out)
 {
     const long rows = p.Kn / p.Hxp;
     const long n = rows * p.Hx;
+    if (p.plane) {
+        k_plane_to_double<T><<<blocks_for(n, 256), 256, 0, p.stream>>>((const T*)p.Khat, out, s,
+                                                                      p.Hx, p.P[1], p.P[2]);
+        MMX_TRY(hipGetLastError());
+        return hipStreamSynchronize(p.stream);
+    }
     k_to_double<T><<<blocks_for(n, 256), 256, 0, p.stream>>>((const T*)p.Khat + s * p.Kn, out, n,
                                                             p.Hx, p.Hxp);
     MMX_TRY(hipGetLastError());
@@ -1285,13 +1368,18 @@ static hipError_t demag_to_S1(Plan& p, const T* m, bool use_ms, const StageIn<T>
     // x forward pass scales by each request's Ms (p.Ms_b)
     const int nc = 3 * p.batch;
     if (p.Pb && (pc || !use_ms || sc || !p.Ms_b || M < 2)) return hipErrorInvalidValue;
+    // plane plans keep the x spectrum transposed, in S2
+    cx<T>* X = p.plane ? S2 : S1;
+    const long xc = p.plane ? p.S2n : s1c;
     MMX_TRY(timed(p, MM_PASS_X_FWD, [&] {
-        return pc ? launch_x_r2c<T, true>(p, M, m, nx, p.N, nx, (const T*)p.Ms_cell, ms, S1, p.Hxp,
-                                          s1c, ny * nz, 3, sc)
-                  : launch_x_r2c<T, false>(p, M, m, nx, p.N, nx, nullptr, ms, S1, p.Hxp, s1c,
-                                           ny * nz, nc, sc);
+        return pc ? launch_x_r2c<T, true>(p, M, m, nx, p.N, nx, (const T*)p.Ms_cell, ms, X, p.Hxp,
+                                          xc, ny * nz, 3, sc, p.plane)
+                  : launch_x_r2c<T, false>(p, M, m, nx, p.N, nx, nullptr, ms, X, p.Hxp, xc,
+                                           ny * nz, nc, sc, p.plane);
     }));
-    if (p.layered) {
+    if (p.plane) {
+        MMX_TRY(timed(p, MM_PASS_MID, [&] { return launch_plane<T>(p); }));
+    } else if (p.layered) {
         if (p.Pb) return hipErrorInvalidValue;
         const long s2c = (long)nz * Py * p.Hxp;
         if (Py > 1)
@@ -1475,7 +1563,7 @@ hipError_t oersted_field(Plan& p, const T* j, T* h_out)
     P.with_demag = 1;
     P.Ms = 1.0;
     Plan r = p;
-    r.percell_A = r.percell_D = r.layered = false;
+    r.percell_A = r.percell_D = r.layered = r.plane = false;
     return launch_local<T, false, 0>(r, p.P[0] / 2, j, h_out, nullptr, P, nullptr);
 }
 
@@ -1972,6 +2060,7 @@ hipError_t field_vjp(Plan& p, const T* m, const T* w, const T* h, unsigned terms
     P.s1_comp = (long)p.n[2] * p.n[1] * p.Hxp;
     P.Hxp = p.Hxp;
     P.with_demag = demag ? 1 : 0;
+    P.tr = p.plane ? 1 : 0;
     P.with_exch = (terms & MM_EXCH) && p.A != 0.0 ? 1 : 0;
     P.with_anis = (terms & MM_ANIS) && p.Ku != 0.0 ? 1 : 0;
     P.Ms = p.Ms;

@@ -163,6 +163,28 @@ __global__ void k_twiddles(cx<T>* tw, int Lmax)
     tw[n] = {(T)c, (T)s};
 }
 
+// Element idx of a uniformly addressed array.  O32: idx * sizeof(P) is below
+// 4 GiB, and the access becomes a scalar base plus a 32-bit vector byte
+// offset (no 64-bit address arithmetic per access).
+template <bool O32, typename P, typename I>
+__device__ __forceinline__ P& elem(P* base, I idx)
+{
+    if constexpr (O32)
+        return *reinterpret_cast<P*>(reinterpret_cast<char*>(base) +
+                                     (unsigned)idx * (unsigned)sizeof(P));
+    else
+        return base[idx];
+}
+template <bool O32, typename P, typename I>
+__device__ __forceinline__ const P& elem(const P* base, I idx)
+{
+    if constexpr (O32)
+        return *reinterpret_cast<const P*>(reinterpret_cast<const char*>(base) +
+                                           (unsigned)idx * (unsigned)sizeof(P));
+    else
+        return base[idx];
+}
+
 // ---------------------------------------------------------------------------
 // F1: x real-to-complex transform of rows of length 2M (M >= 2).
 // Row r of component c reads in[c*in_comp + r*in_row + i] for i < n_in (zero
@@ -193,32 +215,59 @@ __device__ __forceinline__ T stage_elem(const StageIn<T>& sc, const T (&cj)[7],
     return acc;
 }
 
-template <typename T, int M>
+// TR (plane plans): the spectrum goes out as ST[kx][3][nz][nyp], y fastest
+// (plane.h), so a block takes kRows rows that follow each other in y, which
+// makes runs of 64 to 128 bytes; the LDS pitch spreads the rows of one kx
+// over the banks.
+template <typename T, int M, bool TR = false>
 struct XR2C {
     using S = FFTShape<M, Regs<T>::x>;
     static constexpr int kE = S::kE, kT = S::kT;
-    static constexpr int kRows = cmax(1, MMX_XBLOCK / kT);
+    static constexpr int kRows =
+        TR ? (M >= 512 || sizeof(T) == 8 ? 8 : 16) : cmax(1, MMX_XBLOCK / kT);
+    static constexpr int kL = TR ? (S::kLds + 31) / 32 * 32 + 2 : S::kLds;
 };
+// Row pitch of the transposed spectrum.
+__host__ __device__ constexpr int plane_pitch(int ny) { return (ny + 1) & ~1; }
 
 // COMB: the rows are those of a Runge-Kutta stage input y + sum_j c_j k_j
 // (StageIn; `in` is y), formed here in the order and precision of the
 // combination kernel and stored to sc.ys before the Ms scaling.  Ms_b (a
 // batch of requests, components 3b..3b+2 of request b): uniform Ms per
 // request, Ms_b[c / 3] in place of Ms.
-template <typename T, int M, bool PERCELL, bool HALF, bool COMB>
-__global__ __launch_bounds__((XR2C<T, M>::kRows * XR2C<T, M>::kT)) MMX_XR2C_ATTR void k_x_r2c(
+// TR: rows of ny cells' lines per slab (nrows = ny nz), out_comp the spectra's
+// distance between requests (3 components each).
+template <typename T, int M, bool PERCELL, bool HALF, bool COMB, bool TR>
+__global__ __launch_bounds__((XR2C<T, M, TR>::kRows * XR2C<T, M, TR>::kT)) MMX_XR2C_ATTR void k_x_r2c(
     const T* __restrict__ in, long in_row, long in_comp, int n_in, const T* __restrict__ Ms_cell,
     T Ms, cx<T>* __restrict__ out, long out_row, long out_comp, int nrows, int ncomp,
-    const cx<T>* __restrict__ tw, int Lmax, bool vec, StageIn<T> sc, const T* __restrict__ Ms_b)
+    const cx<T>* __restrict__ tw, int Lmax, bool vec, StageIn<T> sc, const T* __restrict__ Ms_b,
+    int ny)
 {
-    using G = XR2C<T, M>;
+    using G = XR2C<T, M, TR>;
     constexpr int kE = G::kE, kT = G::kT, kRows = G::kRows;
-    constexpr int kL = G::S::kLds;  // LDS slots per row
+    constexpr int kL = G::kL;  // LDS slots per row
     __shared__ cx<T> lds[kRows * kL];
     const int t = threadIdx.x % kT, rl = threadIdx.x / kT;
-    const long row = (long)blockIdx.x * kRows + rl;
-    const bool valid = row < (long)nrows * ncomp;
-    const long c = valid ? row / nrows : 0, r = valid ? row % nrows : 0;
+    long c, r;
+    bool valid;
+    int j0 = 0, kz = 0;
+    if constexpr (TR) {
+        const int ntile = (ny + kRows - 1) / kRows, nz = nrows / ny;
+        const long lb = xcd_logical();
+        if (lb >= (long)ntile * nz * ncomp) return;
+        j0 = (int)(lb % ntile) * kRows;
+        const int slab = (int)(lb / ntile);
+        kz = slab % nz;
+        c = slab / nz;
+        valid = j0 + rl < ny;
+        r = (long)kz * ny + (valid ? j0 + rl : 0);
+    } else {
+        const long row = (long)blockIdx.x * kRows + rl;
+        valid = row < (long)nrows * ncomp;
+        c = valid ? row / nrows : 0;
+        r = valid ? row % nrows : 0;
+    }
     const long base = c * in_comp + r * in_row;
     const T* src = in + base;
     const T* msrc = PERCELL ? Ms_cell + r * in_row : nullptr;
@@ -292,11 +341,34 @@ __global__ __launch_bounds__((XR2C<T, M>::kRows * XR2C<T, M>::kT)) MMX_XR2C_ATTR
         }
     }
     cx<T>* L = lds + rl * kL;
-    WgFFT<T, M, Regs<T>::x, -1, HALF>::run(v, t, L, 1, tw, Lmax / M);
-    __syncthreads();
+    WgFFT<T, M, Regs<T>::x, -1, HALF, false, TR>::run(v, t, L, 1, tw, Lmax / M);
+    fft_sync<TR>();
 #pragma unroll
     for (int q = 0; q < kE; ++q) L[G::S::out_index(t, q)] = v[q];
     __syncthreads();
+    if constexpr (TR) {
+        // thread (row j, kk): k = kk + kT q of row j, X_0 + i X_M in column 0
+        const int j = threadIdx.x % kRows, kk = threadIdx.x / kRows;
+        if (j0 + j >= ny) return;
+        const int nz = nrows / ny, nyp = plane_pitch(ny);
+        const cx<T>* R = lds + j * kL;
+        cx<T>* dst = out + (c / 3) * out_comp;
+        const unsigned o0 = (unsigned)((((int)(c % 3)) * nz + kz) * nyp + j0 + j);
+        const unsigned ok = (unsigned)(3 * nz * nyp);
+        const int tws = Lmax / (2 * M);
+#pragma unroll
+        for (int q = 0; q < kE; ++q) {
+            const int k = kk + q * kT;
+            const cx<T> A = R[k], B = cconj(R[(M - k) & (M - 1)]);
+            const cx<T> S = {(T)0.5 * (A.x + B.x), (T)0.5 * (A.y + B.y)};
+            const cx<T> D = {(T)0.5 * (A.x - B.x), (T)0.5 * (A.y - B.y)};
+            const cx<T> wD = cmul(tw[k * tws], D);
+            cx<T> X = {S.x + wD.y, S.y - wD.x};
+            if (k == 0) X = {A.x + A.y, A.x - A.y};
+            elem<true>(dst, o0 + (unsigned)k * ok) = X;
+        }
+        return;
+    }
     if (!valid) return;
     cx<T>* dst = out + c * out_comp + r * out_row;
     const int tws = Lmax / (2 * M);
@@ -313,28 +385,6 @@ __global__ __launch_bounds__((XR2C<T, M>::kRows * XR2C<T, M>::kT)) MMX_XR2C_ATTR
         const cx<T> Z0 = L[0];
         dst[M] = {Z0.x - Z0.y, (T)0};
     }
-}
-
-// Element idx of a uniformly addressed array.  O32: idx * sizeof(P) is below
-// 4 GiB, and the access becomes a scalar base plus a 32-bit vector byte
-// offset (no 64-bit address arithmetic per access).
-template <bool O32, typename P, typename I>
-__device__ __forceinline__ P& elem(P* base, I idx)
-{
-    if constexpr (O32)
-        return *reinterpret_cast<P*>(reinterpret_cast<char*>(base) +
-                                     (unsigned)idx * (unsigned)sizeof(P));
-    else
-        return base[idx];
-}
-template <bool O32, typename P, typename I>
-__device__ __forceinline__ const P& elem(const P* base, I idx)
-{
-    if constexpr (O32)
-        return *reinterpret_cast<const P*>(reinterpret_cast<const char*>(base) +
-                                           (unsigned)idx * (unsigned)sizeof(P));
-    else
-        return base[idx];
 }
 
 // ---------------------------------------------------------------------------
@@ -779,11 +829,12 @@ __device__ inline void atomic_max_nonneg(double* addr, double v)
 // as reals at lds + (rl*3 + c)*kL (x = 0 .. 2M-1, only x < M written).
 // 2M-point real inverse via an M-point complex inverse of
 //   2 Z[n] = (X[n] + conj X[M-n]) + i w^-n (X[n] - conj X[M-n]).
-// Contains barriers: every thread of the block must call it.
-template <typename T, int M>
+// Contains barriers: every thread of the block must call it.  TR: S1 is the
+// transposed spectrum of plane plans (nz layers).
+template <typename T, int M, bool TR = false>
 __device__ __forceinline__ void x_c2r_rows(const cx<T>* __restrict__ S1, cx<T>* lds, int k, int j0,
                                            int ny, long s1_comp, int Hxp,
-                                           const cx<T>* __restrict__ tw, int Lmax)
+                                           const cx<T>* __restrict__ tw, int Lmax, int nz = 1)
 {
     using G = XC2R<T, M>;
     if constexpr (M >= 2) {
@@ -793,7 +844,10 @@ __device__ __forceinline__ void x_c2r_rows(const cx<T>* __restrict__ S1, cx<T>* 
         const int rl = threadIdx.x / (3 * kT);
         const int j = j0 + rl;
         const bool valid = rl < kRows && j < ny;
-        const cx<T>* X = S1 + c * s1_comp + ((long)k * ny + (valid ? j : 0)) * Hxp;
+        const int nyp = plane_pitch(ny);
+        const cx<T>* X = S1 + (TR ? ((long)c * nz + k) * nyp + (valid ? j : 0)
+                                  : c * s1_comp + ((long)k * ny + (valid ? j : 0)) * Hxp);
+        const long xs = TR ? 3L * nz * nyp : 1;
         const int tws = Lmax / (2 * M);
         cx<T> v[kE];
 #pragma unroll
@@ -801,7 +855,11 @@ __device__ __forceinline__ void x_c2r_rows(const cx<T>* __restrict__ S1, cx<T>* 
             const int n = t + r * kT;
             cx<T> z = {0, 0};
             if (valid) {
-                const cx<T> a = X[n], bb = X[M - n];
+                cx<T> a = X[n * xs], bb = X[(TR ? (M - n) & (M - 1) : M - n) * xs];
+                if (TR && n == 0) {  // column 0 holds X_0 + i X_M
+                    bb = {a.y, (T)0};
+                    a.y = 0;
+                }
                 const cx<T> D = {a.x - bb.x, a.y + bb.y};
                 const cx<T> wD = cmulc(D, tw[n * tws]);
                 z = {a.x + bb.x - wD.y, a.y - bb.y + wD.x};
@@ -1078,14 +1136,22 @@ __global__ __launch_bounds__((XC2R<T, M>::kRows * 3 * XC2R<T, M>::kT)) void k_x_
 // per-cell constants of the variant), all with 32-bit offsets from
 // per-component bases; then the transforms, whose real outputs go to LDS,
 // one barrier, and the local terms from registers.
-template <typename T, int M>
+// TR: the spectrum is the transposed one of plane plans, ST[kx][3][nz][nyp]: a
+// block reads kRB values that follow each other in y per (kx, component), two
+// per lane, so its rows are more (runs of 32 to 128 bytes) and its threads
+// with them (two cells each, like the row-major form at M >= 256).
+template <typename T, int M, bool TR = false>
 struct XC2RW {
     static constexpr int kRegs = Regs<T>::x1;
     using S = FFTShape<(M > 0 ? M : 1), kRegs>;
     static constexpr int kE = S::kE, kT = S::kT;
     static constexpr bool kOK = M >= 2 && kT <= 64;     // a transform fits one wavefront
-    static constexpr int kRB = kOK ? cmin(64 / kT, 512 / M) : 1;  // rows per block (kOK)
-    static constexpr int kNT = 256;                               // threads per block
+    static constexpr int kRBT = M >= 256 ? 4 : M >= 32 ? 8 : 16;  // (TR, FP32)
+    static constexpr int kRB = !kOK ? 1
+                               : TR ? (sizeof(T) == 4 ? kRBT : kRBT / 2)
+                                    : cmin(64 / kT, 512 / M);  // rows per block
+    static constexpr int kNT = TR ? cmax(64, kRB * M / 2) : 256;  // threads per block
+    static constexpr int kL = TR ? (S::kLds + 31) / 32 * 32 + 11 : S::kLds;  // LDS row pitch
     static constexpr int kCPT = kOK ? (kRB * M + kNT - 1) / kNT : 1;
     static constexpr int kLogM = ilog2(M > 0 ? M : 1);
     static_assert(!kOK || 3 * kRB * kT <= kNT, "transform threads exceed the block");
@@ -1108,20 +1174,20 @@ struct LocalErr {
 // material and field constants are Pb[b] and its torque maximum goes to
 // torque[b * tstride].  Every address comes from the launch's own geometry
 // (Pk: nx, ny, nz, N, s1_comp, Hxp), never from a request's entry.
-template <typename T, int M, bool PERCELL, int EXT, bool BATCH, bool ERR = false>
-__global__ __launch_bounds__(256) void k_x_c2r_local_w(
+template <typename T, int M, bool TR, bool PERCELL, int EXT, bool BATCH, bool ERR = false>
+__global__ __launch_bounds__((XC2RW<T, M, TR>::kNT)) void k_x_c2r_local_w(
     const cx<T>* __restrict__ S1, const T* __restrict__ m, T* __restrict__ h_out,
     T* __restrict__ dm_out, const T* __restrict__ Ms_cell, const unsigned char* __restrict__ mask,
     LocalParams Pk, double* torque, long nblocks, const cx<T>* __restrict__ tw, int Lmax,
     const T* __restrict__ A_cell, const T* __restrict__ D_cell, const T* __restrict__ zw,
     const T* __restrict__ h_oe, const T* __restrict__ Ku_cell,
     const LocalParams* __restrict__ Pb, int nbatch, long tstride, LocalErr<T> E,
-    const T* __restrict__ m_lo)
+    const T* __restrict__ m_lo, long bstride)
 {
     constexpr bool kDMI = EXT & EXT_DMI, kPA = EXT & EXT_PA, kPD = EXT & EXT_PD;
     constexpr bool kMIX = EXT & EXT_MIX, kLO = EXT & EXT_LO;
-    using G = XC2RW<T, M>;
-    constexpr int kE = G::kE, kT = G::kT, RB = G::kRB, CPT = G::kCPT, kL = G::S::kLds;
+    using G = XC2RW<T, M, TR>;
+    constexpr int kE = G::kE, kT = G::kT, RB = G::kRB, CPT = G::kCPT, kL = G::kL;
     constexpr int NTW = (M + G::kNT - 1) / G::kNT;
     __shared__ cx<T> lds[3 * RB * kL];
     __shared__ cx<T> twl[M];  // the M-point transform's twiddles
@@ -1132,7 +1198,7 @@ __global__ __launch_bounds__(256) void k_x_c2r_local_w(
         bi = (int)(lb / nblocks);
         lb -= (long)bi * nblocks;
         const long n3 = 3 * Pk.N;
-        S1 += (long)bi * 3 * Pk.s1_comp;
+        S1 += (long)bi * bstride;
         m += (long)bi * n3;
         if constexpr (kLO) m_lo += (long)bi * n3;
         if (h_out) h_out += (long)bi * n3;
@@ -1157,8 +1223,25 @@ __global__ __launch_bounds__(256) void k_x_c2r_local_w(
     const int tau = tid / kT, t = tid % kT;
     const int frl = tau / 3, fc = tau % 3;
     const bool frow = with_demag && fthr && j0 + frl < ny;
-    cx<T> xa[kE], xb[kE];
-    {
+    cx<T> xa[TR ? 1 : kE], xb[TR ? 1 : kE];
+    // TR: pairs of rows (2 jp, 2 jp + 1) of (kx, component)
+    constexpr int NPR = TR ? RB / 2 : 1, NLD = TR ? (M * 3 * NPR + G::kNT - 1) / G::kNT : 1;
+    struct alignas(2 * sizeof(cx<T>)) cx2 {
+        cx<T> a, b;
+    };
+    cx2 xt[NLD];
+    if constexpr (TR) {
+        const int nyp = plane_pitch(ny);
+        const unsigned o0 = (unsigned)(k * nyp + j0), oc = (unsigned)(nz * nyp);
+#pragma unroll
+        for (int q = 0; q < NLD; ++q) {
+            const int i = tid + G::kNT * q, jp = i % NPR, col = i / NPR;  // col = 3 kx + c
+            const bool use = with_demag && i < M * 3 * NPR && j0 + 2 * jp < ny;
+            xt[q] = use ? *reinterpret_cast<const cx2*>(
+                              &elem<true>(S1, o0 + (unsigned)(2 * jp) + (unsigned)col * oc))
+                        : cx2{{0, 0}, {0, 0}};
+        }
+    } else {
         const cx<T>* X =
             S1 + (long)fc * Pk.s1_comp + ((long)k * ny + (frow ? j0 + frl : 0)) * Pk.Hxp;
 #pragma unroll
@@ -1233,6 +1316,17 @@ __global__ __launch_bounds__(256) void k_x_c2r_local_w(
         const int n = tid + G::kNT * q;
         if (n < M) twl[n] = twv[q];
     }
+    if constexpr (TR) {
+#pragma unroll
+        for (int q = 0; q < NLD; ++q) {
+            const int i = tid + G::kNT * q, jp = i % NPR, col = i / NPR;
+            if (i < M * 3 * NPR) {
+                cx<T>* L = lds + (2 * jp * 3 + col % 3) * kL + col / 3;
+                L[0] = xt[q].a;
+                L[3 * kL] = xt[q].b;
+            }
+        }
+    }
     __syncthreads();
     T* hd = reinterpret_cast<T*>(lds + (frl * 3 + fc) * kL);
     if (with_demag && fthr) {
@@ -1241,11 +1335,24 @@ __global__ __launch_bounds__(256) void k_x_c2r_local_w(
 #pragma unroll
         for (int r = 0; r < kE; ++r) {
             const int n = t + r * kT;
-            const cx<T> a = xa[r], bb = xb[r];
+            cx<T> a, bb;
+            if constexpr (TR) {
+                const cx<T>* X = lds + (frl * 3 + fc) * kL;
+                a = X[n];
+                bb = X[(M - n) & (M - 1)];
+                if (n == 0) {  // column 0 holds X_0 + i X_M
+                    bb = {a.y, (T)0};
+                    a.y = 0;
+                }
+            } else {
+                a = xa[r];
+                bb = xb[r];
+            }
             const cx<T> D = {a.x - bb.x, a.y + bb.y};
             const cx<T> wD = cmulc(D, tw[n * tws]);
             v[r] = {a.x + bb.x - wD.y, a.y - bb.y + wD.x};
         }
+        if constexpr (TR) fft_sync<true>();  // the reads above precede the first exchange
         WgFFT<T, M, G::kRegs, 1, false, false, true>::run(v, t, lds + (frl * 3 + fc) * kL, 1, twl,
                                                           1);
         fft_sync<true>();  // the transform's last exchange reads precede these writes
@@ -1517,20 +1624,24 @@ hipError_t launch_strided(const Plan& p, int L, const cx<T>* in, cx<T>* out, int
 template <typename T, int M, bool PC>
 static hipError_t launch_x_r2c_M(const Plan& p, const T* in, long in_row, long in_comp, int n_in,
                                  const T* Ms_cell, T Ms, cx<T>* out, long out_row, long out_comp,
-                                 int nrows, int ncomp, const StageIn<T>* sc);
+                                 int nrows, int ncomp, const StageIn<T>* sc, bool tr);
 
+// tr: the transposed spectrum of plane plans (out_comp: distance between
+// requests, out_row unused).
 template <typename T, bool PC>
 hipError_t launch_x_r2c(const Plan& p, int M, const T* in, long in_row, long in_comp,
                                int n_in, const T* Ms_cell, T Ms, cx<T>* out, long out_row,
-                               long out_comp, int nrows, int ncomp, const StageIn<T>* sc = nullptr)
+                               long out_comp, int nrows, int ncomp, const StageIn<T>* sc = nullptr,
+                               bool tr = false)
 {
     // a stage input needs the transform kernel (M >= 2) and in == sc->y
     if (sc && (M < 2 || in != sc->y || !sc->ys)) return hipErrorInvalidValue;
+    if (tr && (M < 2 || nrows % p.n[1] != 0)) return hipErrorInvalidValue;
     switch (M) {
 #define MMX_X(LL)                                                                                 \
     case LL:                                                                                      \
         return launch_x_r2c_M<T, LL, PC>(p, in, in_row, in_comp, n_in, Ms_cell, Ms, out, out_row, \
-                                         out_comp, nrows, ncomp, sc);
+                                         out_comp, nrows, ncomp, sc, tr);
         MMX_X(0) MMX_CASES(MMX_X)
 #undef MMX_X
     }
@@ -1553,7 +1664,7 @@ __global__ void k_x_copy(const T* __restrict__ in, long in_row, long in_comp, in
 template <typename T, int M, bool PC>
 static hipError_t launch_x_r2c_M(const Plan& p, const T* in, long in_row, long in_comp, int n_in,
                                  const T* Ms_cell, T Ms, cx<T>* out, long out_row, long out_comp,
-                                 int nrows, int ncomp, const StageIn<T>* sc)
+                                 int nrows, int ncomp, const StageIn<T>* sc, bool tr)
 {
     const long rows = (long)nrows * ncomp;
     if constexpr (M == 0 || M == 1) {
@@ -1562,7 +1673,11 @@ static hipError_t launch_x_r2c_M(const Plan& p, const T* in, long in_row, long i
                                                                    nrows, ncomp);
     } else {
         using G = XR2C<T, M>;
-        const long grid = (rows + G::kRows - 1) / G::kRows;
+        using GT = XR2C<T, M, true>;
+        const int ny = p.n[1];
+        const long grid =
+            tr ? xcd_grid((long)((ny + GT::kRows - 1) / GT::kRows) * (nrows / ny) * ncomp)
+               : (rows + G::kRows - 1) / G::kRows;
         const uintptr_t al = 2 * sizeof(T) - 1;
         bool vec = n_in % 2 == 0 && in_row % 2 == 0 && in_comp % 2 == 0 &&
                    ((uintptr_t)in & al) == 0 && (!PC || ((uintptr_t)Ms_cell & al) == 0);
@@ -1573,19 +1688,27 @@ static hipError_t launch_x_r2c_M(const Plan& p, const T* in, long in_row, long i
                     vec = vec && ((uintptr_t)sc->k[j] & al) == 0;
         }
         const StageIn<T> none{};
-        const dim3 blk(G::kRows * G::kT);
-#define MMX_XL(HF, CB)                                                                          \
-    k_x_r2c<T, M, PC, HF, CB><<<grid, blk, 0, p.stream>>>(in, in_row, in_comp, n_in, Ms_cell, Ms, \
-                                                          out, out_row, out_comp, nrows, ncomp, \
-                                                          (const cx<T>*)p.tw, p.Lmax, vec,      \
-                                                          CB ? *sc : none,                      \
-                                                          PC ? nullptr : (const T*)p.Ms_b)
+        const dim3 blk(tr ? GT::kRows * GT::kT : G::kRows * G::kT);
+#define MMX_XLT(HF, CB, TR)                                                                     \
+    k_x_r2c<T, M, PC, HF, CB, TR><<<grid, blk, 0, p.stream>>>(                                  \
+        in, in_row, in_comp, n_in, Ms_cell, Ms, out, out_row, out_comp, nrows, ncomp,           \
+        (const cx<T>*)p.tw, p.Lmax, vec, CB ? *sc : none, PC ? nullptr : (const T*)p.Ms_b, ny)
+#define MMX_XL(HF, CB) MMX_XLT(HF, CB, false)
+        if constexpr (M <= 512) {
+            if (tr) {
+                // plane plans: cells only (n_in <= M)
+                if (n_in > M) return hipErrorInvalidValue;
+                if (sc) MMX_XLT(true, true, true); else MMX_XLT(true, false, true);
+                return hipGetLastError();
+            }
+        }
         if (n_in <= M) {
             if (sc) MMX_XL(true, true); else MMX_XL(true, false);
         } else {
             if (sc) MMX_XL(false, true); else MMX_XL(false, false);
         }
 #undef MMX_XL
+#undef MMX_XLT
     }
     return hipGetLastError();
 }
@@ -1672,76 +1795,85 @@ hipError_t launch_mid(const Plan& p, int L, cx<T>* S, int n_valid, long es, long
 
 // err: also accumulate the error norm's block partials (plain stencil, one
 // request, wave-local kernel); *nb_out: the number of blocks (partial pairs).
+template <typename T, int M, bool PC, int EXT, bool TR>
+static hipError_t launch_local_W(const Plan& p, const T* m, T* h, T* dm, const LocalParams& P,
+                                 double* torque, const LocalErr<T>* err, long* nb_out,
+                                 const T* m_lo)
+{
+    using Gw = XC2RW<T, M, TR>;
+    const int njt = (p.n[1] + Gw::kRB - 1) / Gw::kRB;
+    const long nblocks = (long)njt * p.n[2];
+    if (nb_out) *nb_out = nblocks;
+    const cx<T>* S = (const cx<T>*)(TR ? p.S2 : p.S1);
+    const cx<T>* tw = (const cx<T>*)p.tw;
+    const long bstride = TR ? p.S2n : p.S1n;
+    const LocalErr<T> no{};
+    const T* none = nullptr;
+    const T* h_oe = P.with_oe ? (const T*)p.h_oe : none;
+    const T* zw = p.layered ? (const T*)p.zw : none;
+    if (m_lo) {
+        // the split state (FP32 fields of a double state): plain stencil,
+        // one material per request
+        if constexpr (std::is_same<T, float>::value && !PC && EXT == 0) {
+            if (err || p.layered) return hipErrorInvalidValue;
+            if (p.Pb)
+                k_x_c2r_local_w<T, M, TR, false, EXT_LO, true>
+                    <<<xcd_grid(nblocks * p.batch), Gw::kNT, 0, p.stream>>>(
+                        S, m, h, dm, none, nullptr, P, torque, nblocks, tw, p.Lmax, none, none,
+                        none, none, none, (const LocalParams*)p.Pb, p.batch, 8, no, m_lo, bstride);
+            else
+                k_x_c2r_local_w<T, M, TR, false, EXT_LO, false>
+                    <<<xcd_grid(nblocks), Gw::kNT, 0, p.stream>>>(
+                        S, m, h, dm, none, p.mask, P, torque, nblocks, tw, p.Lmax, none, none,
+                        none, h_oe, none, nullptr, 1, 0, no, m_lo, bstride);
+            return hipGetLastError();
+        }
+        return hipErrorInvalidValue;
+    }
+    if (err) {
+        if constexpr (EXT == 0) {
+            if (p.Pb || !dm || !err->part || nblocks > (long)p.n[1] * p.n[2])
+                return hipErrorInvalidValue;
+            k_x_c2r_local_w<T, M, TR, PC, 0, false, true>
+                <<<xcd_grid(nblocks), Gw::kNT, 0, p.stream>>>(
+                    S, m, h, dm, (const T*)p.Ms_cell, p.mask, P, torque, nblocks, tw, p.Lmax, none,
+                    none, zw, h_oe, none, nullptr, 1, 0, *err, none, bstride);
+            return hipGetLastError();
+        }
+        return hipErrorInvalidValue;
+    }
+    if (p.Pb) {
+        // a batch plan: uniform material per request, constants from
+        // p.Pb, p.batch requests per launch, torque maxima 8 doubles apart
+        if constexpr (!PC && EXT == 0) {
+            if (p.layered || p.batch < 1) return hipErrorInvalidValue;
+            k_x_c2r_local_w<T, M, TR, false, 0, true>
+                <<<xcd_grid(nblocks * p.batch), Gw::kNT, 0, p.stream>>>(
+                    S, m, h, dm, none, nullptr, P, torque, nblocks, tw, p.Lmax, none, none, none,
+                    none, none, (const LocalParams*)p.Pb, p.batch, 8, no, none, bstride);
+            return hipGetLastError();
+        }
+        return hipErrorInvalidValue;
+    }
+    k_x_c2r_local_w<T, M, TR, PC, EXT, false><<<xcd_grid(nblocks), Gw::kNT, 0, p.stream>>>(
+        S, m, h, dm, (const T*)p.Ms_cell, p.mask, P, torque, nblocks, tw, p.Lmax,
+        (EXT & EXT_PA) ? (const T*)p.A_cell : none, (EXT & EXT_PD) ? (const T*)p.D_cell : none, zw,
+        h_oe, EXT != 0 && p.percell_Ku ? (const T*)p.Ku_cell : none, nullptr, 1, 0, no, none,
+        bstride);
+    return hipGetLastError();
+}
+
 template <typename T, int M, bool PC, int EXT>
 static hipError_t launch_local_M(const Plan& p, const T* m, T* h, T* dm, const LocalParams& P,
                                  double* torque, const LocalErr<T>* err, long* nb_out,
                                  const T* m_lo)
 {
     if constexpr (MMX_X1W && XC2RW<T, M>::kOK) {
-        using Gw = XC2RW<T, M>;
-        const int njt = (p.n[1] + Gw::kRB - 1) / Gw::kRB;
-        const long nblocks = (long)njt * p.n[2];
-        if (nb_out) *nb_out = nblocks;
-        if (m_lo) {
-            // the split state (FP32 fields of a double state): plain stencil,
-            // one material per request
-            if constexpr (std::is_same<T, float>::value && !PC && EXT == 0) {
-                if (err || p.layered) return hipErrorInvalidValue;
-                if (p.Pb) {
-                    k_x_c2r_local_w<T, M, false, EXT_LO, true>
-                        <<<xcd_grid(nblocks * p.batch), Gw::kNT, 0, p.stream>>>(
-                            (const cx<T>*)p.S1, m, h, dm, nullptr, nullptr, P, torque, nblocks,
-                            (const cx<T>*)p.tw, p.Lmax, nullptr, nullptr, nullptr, nullptr,
-                            nullptr, (const LocalParams*)p.Pb, p.batch, 8, LocalErr<T>{}, m_lo);
-                } else {
-                    k_x_c2r_local_w<T, M, false, EXT_LO, false>
-                        <<<xcd_grid(nblocks), Gw::kNT, 0, p.stream>>>(
-                            (const cx<T>*)p.S1, m, h, dm, nullptr, p.mask, P, torque, nblocks,
-                            (const cx<T>*)p.tw, p.Lmax, nullptr, nullptr, nullptr,
-                            P.with_oe ? (const T*)p.h_oe : nullptr, nullptr, nullptr, 1, 0,
-                            LocalErr<T>{}, m_lo);
-                }
-                return hipGetLastError();
-            }
-            return hipErrorInvalidValue;
-        }
-        if (err) {
-            if constexpr (EXT == 0) {
-                if (p.Pb || !dm || !err->part || nblocks > (long)p.n[1] * p.n[2])
-                    return hipErrorInvalidValue;
-                k_x_c2r_local_w<T, M, PC, 0, false, true>
-                    <<<xcd_grid(nblocks), Gw::kNT, 0, p.stream>>>(
-                        (const cx<T>*)p.S1, m, h, dm, (const T*)p.Ms_cell, p.mask, P, torque,
-                        nblocks, (const cx<T>*)p.tw, p.Lmax, nullptr, nullptr,
-                        p.layered ? (const T*)p.zw : nullptr, P.with_oe ? (const T*)p.h_oe : nullptr,
-                        nullptr, nullptr, 1, 0, *err, nullptr);
-                return hipGetLastError();
-            }
-            return hipErrorInvalidValue;
-        }
-        if (p.Pb) {
-            // a batch plan: uniform material per request, constants from
-            // p.Pb, p.batch requests per launch, torque maxima 8 doubles apart
-            if constexpr (!PC && EXT == 0) {
-                if (p.layered || p.batch < 1) return hipErrorInvalidValue;
-                k_x_c2r_local_w<T, M, false, 0, true>
-                    <<<xcd_grid(nblocks * p.batch), Gw::kNT, 0, p.stream>>>(
-                        (const cx<T>*)p.S1, m, h, dm, nullptr, nullptr, P, torque, nblocks,
-                        (const cx<T>*)p.tw, p.Lmax, nullptr, nullptr, nullptr, nullptr, nullptr,
-                        (const LocalParams*)p.Pb, p.batch, 8, LocalErr<T>{}, nullptr);
-                return hipGetLastError();
-            }
-            return hipErrorInvalidValue;
-        }
-        k_x_c2r_local_w<T, M, PC, EXT, false><<<xcd_grid(nblocks), Gw::kNT, 0, p.stream>>>(
-            (const cx<T>*)p.S1, m, h, dm, (const T*)p.Ms_cell, p.mask, P, torque, nblocks,
-            (const cx<T>*)p.tw, p.Lmax, (EXT & EXT_PA) ? (const T*)p.A_cell : nullptr,
-            (EXT & EXT_PD) ? (const T*)p.D_cell : nullptr, p.layered ? (const T*)p.zw : nullptr,
-            P.with_oe ? (const T*)p.h_oe : nullptr,
-            EXT != 0 && p.percell_Ku ? (const T*)p.Ku_cell : nullptr, nullptr, 1, 0,
-            LocalErr<T>{}, nullptr);
-        return hipGetLastError();
+        return p.plane
+                   ? launch_local_W<T, M, PC, EXT, true>(p, m, h, dm, P, torque, err, nb_out, m_lo)
+                   : launch_local_W<T, M, PC, EXT, false>(p, m, h, dm, P, torque, err, nb_out, m_lo);
     }
+    if (p.plane) return hipErrorInvalidValue;
     // batches, the error accumulation and the split state need the
     // wave-local kernel
     if (p.Pb || err || m_lo) return hipErrorInvalidValue;
@@ -1811,10 +1943,10 @@ hipError_t launch_local_ext(const Plan& p, int M, const T* m, T* h, T* dm, const
                                                   long, long);                                  \
     EXT_ template hipError_t launch_x_r2c<T, false>(const Plan&, int, const T*, long, long, int, \
                                                     const T*, T, cx<T>*, long, long, int, int,  \
-                                                    const StageIn<T>*);                         \
+                                                    const StageIn<T>*, bool);                   \
     EXT_ template hipError_t launch_x_r2c<T, true>(const Plan&, int, const T*, long, long, int,  \
                                                    const T*, T, cx<T>*, long, long, int, int,   \
-                                                   const StageIn<T>*);                          \
+                                                   const StageIn<T>*, bool);                    \
     EXT_ template hipError_t launch_local<T, false, 0>(const Plan&, int, const T*, T*, T*,      \
                                                        const LocalParams&, double*,             \
                                                        const LocalErr<T>*, long*, const T*);    \
