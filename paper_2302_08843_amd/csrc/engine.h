@@ -51,6 +51,9 @@ struct Plan {
     double d[3];   // dx, dy, dz
     int P[3];      // padded extents
     int Hx;        // Px/2 + 1 (1 when Px == 1): x bins kept by the real transform
+    int Hc;        // columns the x, y and z passes write: Hx rounded up to 128 bytes of complex
+                   // values (partly written lines cost more: y forward 274 us against 256 at
+                   // 512x512x64 FP32)
     int Hxp;       // row stride of every spectral array (Hx rounded up to 128 bytes of reals)
     long N;        // cells
     long S1n;      // complex values in S1 = 3 * nz * ny * Hxp
@@ -85,7 +88,8 @@ struct Plan {
     hipStream_t stream;
     int ncu = 256;  // compute units of the device (persistent launches)
     // device buffers (element type = plan precision unless noted)
-    void *Khat = nullptr;     // [6][Pz/2+1][Py/2+1][Hxp] real, scaled by 1/(Px Py Pz); plane:
+    void *Khat = nullptr;     // 6 (Pz/2+1)(Py/2+1) Hxp reals, scaled by 1/(Px Py Pz), in column
+                              // tiles (mid_index); layered [6][pairs][Py/2+1][Hxp]; plane:
                               // [Px/2+1][ky parity][6][Pz/2+1][ky/2] in the same buffer
     void *S1 = nullptr;       // [3][nz][ny][Hxp] complex (plane: scratch of k_plane)
     void *S2 = nullptr;       // [3][nz][Py][Hxp] complex (aliases S1 when Py == 1); plane: the x
@@ -98,7 +102,7 @@ struct Plan {
     void *zw = nullptr;       // layered: 4 reals per layer (z exchange down/up, 1/(2 dz_k), 0)
     double *lw = nullptr;     // layered: nz doubles, the layer heights (energy weights)
     // Oersted field (allocated on first use)
-    void *oe_G = nullptr;     // [3][Pz/2+1][Py/2+1][Hxp] real: Im of the kernel spectrum / (Px Py Pz)
+    void *oe_G = nullptr;     // 3 (Pz/2+1)(Py/2+1) Hxp reals (mid_index): Im of the kernel spectrum / (Px Py Pz)
     void *h_oe = nullptr;     // 3N reals: field of the set current density
     bool oe_on = false;       // Oersted term present (mm_set_current)
     double oe_freq = 0.0;     // h_oe scaled by sin(2 pi f t) when f != 0

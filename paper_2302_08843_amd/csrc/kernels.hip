@@ -828,15 +828,16 @@ __global__ void k_place(double* __restrict__ R, int s, int nx, int ny, int nz, i
 // Keep the real part of the transformed component (it is real by parity) for
 // 0 <= ky <= Py/2, 0 <= kz <= Pz/2, scaled by 1/(Px Py Pz).
 template <typename T>
-__global__ void k_fold(T* __restrict__ Khat, const cx<double>* __restrict__ C, int Hx, int Hxp,
-                       int Py, int Pz, double scale)
+__global__ void k_fold(T* __restrict__ Khat, const cx<double>* __restrict__ C, int s, int Hx,
+                       int Hxp, int Py, int Pz, int kw, double scale)
 {
     const int hy = Py / 2 + 1, hz = Pz / 2 + 1;
     const long total = (long)hz * hy * Hxp;
     const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= total) return;
     const int kx = (int)(q % Hxp), ky = (int)((q / Hxp) % hy), kz = (int)(q / ((long)Hxp * hy));
-    Khat[q] = kx < Hx ? (T)(C[((long)kz * Py + ky) * Hxp + kx].x * scale) : (T)0;
+    Khat[mid_index(6, s, kx, ky, kz, Py, Pz, Hxp, kw)] =
+        kx < Hx ? (T)(C[((long)kz * Py + ky) * Hxp + kx].x * scale) : (T)0;
 }
 
 #define MMX_TRY_PROF(x)                   \
@@ -1201,20 +1202,22 @@ hipError_t build_tensor(Plan& p)
                 (T*)p.Khat, C, s, p.Hx, p.Hxp, Py, Pz, 1.0 / (double)PN);
         else
             k_fold<T><<<blocks_for(p.Kn, 256), 256, 0, p.stream>>>(
-                (T*)p.Khat + s * p.Kn, C, p.Hx, p.Hxp, Py, Pz, 1.0 / (double)PN);
+                (T*)p.Khat, C, s, p.Hx, p.Hxp, Py, Pz, mid_kw(sizeof(T), Pz > 1 ? Pz : Py),
+                1.0 / (double)PN);
         MMX_TRY(hipGetLastError());
     }
     return hipStreamSynchronize(p.stream);
 }
 
+// out[kz][ky][kx] (kx < Hx) = component s of the kernel spectrum.
 template <typename T>
-__global__ void k_to_double(const T* in, double* out, long n, int Hx, int Hxp)
+__global__ void k_to_double(const T* in, double* out, int s, int Hx, int Hxp, int Py, int Pz, int kw)
 {
-    // drop the row padding: (rows x Hxp) -> (rows x Hx)
+    const int hy = Py / 2 + 1, hz = Pz / 2 + 1;
     const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= n) return;
-    const long row = q / Hx, kx = q % Hx;
-    out[q] = (double)in[row * Hxp + kx];
+    if (q >= (long)hz * hy * Hx) return;
+    const int kx = (int)(q % Hx), ky = (int)((q / Hx) % hy), kz = (int)(q / ((long)Hx * hy));
+    out[q] = (double)in[mid_index(6, s, kx, ky, kz, Py, Pz, Hxp, kw)];
 }
 
 // The same from the plane layout.
@@ -1239,8 +1242,9 @@ hipError_t debug_spectrum(Plan& p, int s, double* out)
         MMX_TRY(hipGetLastError());
         return hipStreamSynchronize(p.stream);
     }
-    k_to_double<T><<<blocks_for(n, 256), 256, 0, p.stream>>>((const T*)p.Khat + s * p.Kn, out, n,
-                                                            p.Hx, p.Hxp);
+    const int Py = p.P[1], Pz = p.P[2];
+    k_to_double<T><<<blocks_for(n, 256), 256, 0, p.stream>>>(
+        (const T*)p.Khat, out, s, p.Hx, p.Hxp, Py, Pz, mid_kw(sizeof(T), Pz > 1 ? Pz : Py));
     MMX_TRY(hipGetLastError());
     return hipStreamSynchronize(p.stream);
 }
@@ -1339,9 +1343,9 @@ static hipError_t launch_zdense(Plan& p, cx<T>* S)
     constexpr int TW = ZdTile<T>::kTW;
     const int nz = p.n[2], Py = p.P[1];
     const int G = nz < kZdMaxLayers ? nz : kZdMaxLayers;
-    dim3 grid((unsigned)((p.Hx + TW - 1) / TW), (unsigned)(Py / 2 + 1));
+    dim3 grid((unsigned)((p.Hc + TW - 1) / TW), (unsigned)(Py / 2 + 1));
     const size_t lds = sizeof(cx<T>) * 2 * 3 * nz * TW;
-    k_zdense<T><<<grid, TW * G, lds, p.stream>>>(S, (const T*)p.Khat, nz, Py, p.Hx, p.Hxp,
+    k_zdense<T><<<grid, TW * G, lds, p.stream>>>(S, (const T*)p.Khat, nz, Py, p.Hc, p.Hxp,
                                                  (long)nz * Py * p.Hxp, p.Kn, p.lw,
                                                  layer_ref(p));
     return hipGetLastError();
@@ -1384,20 +1388,20 @@ static hipError_t demag_to_S1(Plan& p, const T* m, bool use_ms, const StageIn<T>
         const long s2c = (long)nz * Py * p.Hxp;
         if (Py > 1)
             MMX_TRY(timed(p, MM_PASS_Y_FWD, [&] {
-                return launch_strided<T, -1>(p, Py, S1, S2, ny, Py, p.Hxp, p.Hxp, p.Hx, 3, s1c, s2c,
+                return launch_strided<T, -1>(p, Py, S1, S2, ny, Py, p.Hxp, p.Hxp, p.Hc, 3, s1c, s2c,
                                              nz, (long)ny * p.Hxp, (long)Py * p.Hxp);
             }));
         MMX_TRY(timed(p, MM_PASS_MID, [&] { return launch_zdense<T>(p, Py > 1 ? S2 : S1); }));
         if (Py > 1)
             MMX_TRY(timed(p, MM_PASS_Y_INV, [&] {
-                return launch_strided<T, 1>(p, Py, S2, S1, Py, ny, p.Hxp, p.Hxp, p.Hx, 3, s2c, s1c,
+                return launch_strided<T, 1>(p, Py, S2, S1, Py, ny, p.Hxp, p.Hxp, p.Hc, 3, s2c, s1c,
                                             nz, (long)Py * p.Hxp, (long)ny * p.Hxp);
             }));
     } else if (Pz > 1) {
         const long s2c = (long)nz * Py * p.Hxp;
         if (Py > 1)
             MMX_TRY(timed(p, MM_PASS_Y_FWD, [&] {
-                return launch_strided<T, -1>(p, Py, S1, S2, ny, Py, p.Hxp, p.Hxp, p.Hx, nc, s1c, s2c,
+                return launch_strided<T, -1>(p, Py, S1, S2, ny, Py, p.Hxp, p.Hxp, p.Hc, nc, s1c, s2c,
                                              nz, (long)ny * p.Hxp, (long)Py * p.Hxp);
             }));
         MMX_TRY(timed(p, MM_PASS_MID, [&] {
@@ -1405,7 +1409,7 @@ static hipError_t demag_to_S1(Plan& p, const T* m, bool use_ms, const StageIn<T>
         }));
         if (Py > 1)
             MMX_TRY(timed(p, MM_PASS_Y_INV, [&] {
-                return launch_strided<T, 1>(p, Py, S2, S1, Py, ny, p.Hxp, p.Hxp, p.Hx, nc, s2c, s1c,
+                return launch_strided<T, 1>(p, Py, S2, S1, Py, ny, p.Hxp, p.Hxp, p.Hc, nc, s2c, s1c,
                                             nz, (long)Py * p.Hxp, (long)ny * p.Hxp);
             }));
     } else {
@@ -1462,15 +1466,16 @@ __global__ void k_oe_place(double* __restrict__ R, int comp, int nx, int ny, int
 }
 
 template <typename T>
-__global__ void k_oe_fold(T* __restrict__ G, const cx<double>* __restrict__ C, int Hx, int Hxp,
-                          int Py, int Pz, double scale)
+__global__ void k_oe_fold(T* __restrict__ G, const cx<double>* __restrict__ C, int s, int Hx,
+                          int Hxp, int Py, int Pz, int kw, double scale)
 {
     const int hy = Py / 2 + 1, hz = Pz / 2 + 1;
     const long total = (long)hz * hy * Hxp;
     const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= total) return;
     const int kx = (int)(q % Hxp), ky = (int)((q / Hxp) % hy), kz = (int)(q / ((long)Hxp * hy));
-    G[q] = kx < Hx ? (T)(C[((long)kz * Py + ky) * Hxp + kx].y * scale) : (T)0;
+    G[mid_index(3, s, kx, ky, kz, Py, Pz, Hxp, kw)] =
+        kx < Hx ? (T)(C[((long)kz * Py + ky) * Hxp + kx].y * scale) : (T)0;
 }
 
 template <typename T>
@@ -1517,8 +1522,9 @@ static hipError_t oersted_setup(Plan& p)
             MMX_TRY((launch_strided<double, -1>(q, Pz, C, C, Pz, Pz, (long)Py * p.Hxp,
                                                 (long)Py * p.Hxp, p.Hx, 1, 0, 0, Py, p.Hxp,
                                                 p.Hxp)));
-        k_oe_fold<T><<<blocks_for(gn, 256), 256, 0, p.stream>>>((T*)p.oe_G + comp * gn, C, p.Hx,
-                                                                p.Hxp, Py, Pz, 1.0 / (double)PN);
+        k_oe_fold<T><<<blocks_for(gn, 256), 256, 0, p.stream>>>(
+            (T*)p.oe_G, C, comp, p.Hx, p.Hxp, Py, Pz, mid_kw(sizeof(T), Pz > 1 ? Pz : Py),
+            1.0 / (double)PN);
         MMX_TRY(hipGetLastError());
     }
     return hipStreamSynchronize(p.stream);
@@ -1543,11 +1549,11 @@ hipError_t oersted_field(Plan& p, const T* j, T* h_out)
     if (Pz > 1) {
         const long s2c = (long)nz * Py * p.Hxp;
         if (Py > 1)
-            MMX_TRY((launch_strided<T, -1>(p, Py, S1, S2, ny, Py, p.Hxp, p.Hxp, p.Hx, 3, s1c, s2c,
+            MMX_TRY((launch_strided<T, -1>(p, Py, S1, S2, ny, Py, p.Hxp, p.Hxp, p.Hc, 3, s1c, s2c,
                                            nz, (long)ny * p.Hxp, (long)Py * p.Hxp)));
         MMX_TRY((launch_mid<T, 2, 1>(q, Pz, S2, nz, (long)Py * p.Hxp, s2c, p.Hxp, Py)));
         if (Py > 1)
-            MMX_TRY((launch_strided<T, 1>(p, Py, S2, S1, Py, ny, p.Hxp, p.Hxp, p.Hx, 3, s2c, s1c,
+            MMX_TRY((launch_strided<T, 1>(p, Py, S2, S1, Py, ny, p.Hxp, p.Hxp, p.Hc, 3, s2c, s1c,
                                           nz, (long)Py * p.Hxp, (long)ny * p.Hxp)));
     } else {
         MMX_TRY((launch_mid<T, 1, 1>(q, Py, S1, ny, p.Hxp, s1c, 0, 1)));

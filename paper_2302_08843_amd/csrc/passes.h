@@ -381,9 +381,10 @@ __global__ __launch_bounds__((XR2C<T, M, TR>::kRows * XR2C<T, M, TR>::kT)) MMX_X
         const cx<T> wD = cmul(tw[k * tws], D);
         dst[k] = {S.x + wD.y, S.y - wD.x};  // S - i wD
     }
-    if (t == 0) {
+    // the last column, and zeros up to the end of its 128 bytes
+    if (t < 128 / (int)sizeof(cx<T>) && M + t < out_row) {
         const cx<T> Z0 = L[0];
-        dst[M] = {Z0.x - Z0.y, (T)0};
+        dst[M + t] = {t == 0 ? Z0.x - Z0.y : (T)0, (T)0};
     }
 }
 
@@ -471,16 +472,41 @@ struct Mid {
 // G: the thread shape (kE registers, kT threads per transform); the
 // transform's LDS scratch is lds[s * lstride].  WAVE: the kT threads of a
 // transform share one wavefront (exchanges without workgroup barriers).
+// Layout of the folded spectral kernel for the last-axis pass along an axis of
+// padded length L: [group][column tile][NK components][L/2+1][KW columns]
+// (group ky when the pass runs along z, one group when it runs along y), so
+// that the tile a block needs is one contiguous piece.  With one component's
+// plane after the other ([NK][Pz/2+1][Py/2+1][Hxp], 32-byte pieces a kernel
+// plane apart) the z pass took 530 us at 512x512x64 FP32 and 1000 in FP64,
+// with this 461 and 877 (its loads and stores alone, without the transforms:
+// 532 us before, 340 without the kernel's).
+__host__ __device__ constexpr int mid_kw(int prec_bytes, int L)
+{
+    const int regs = prec_bytes == 4 ? MMX_RMW_F32 : MMX_RMW_F64;
+    const int T = L / (regs < L ? regs : L);  // threads per transform
+    const int cb = T <= 64 ? 64 / T : 1, most = 128 / prec_bytes;
+    return cb < most ? cb : most;
+}
+// Offset of column kx, ky, kz (folded) of component c.
+__host__ __device__ inline long mid_index(int nk, int c, int kx, int ky, int kz, int Py, int Pz,
+                                          int Hxp, int kw)
+{
+    const long g = Pz > 1 ? ky : 0, r = Pz > 1 ? kz : ky, R = (Pz > 1 ? Pz : Py) / 2 + 1;
+    return (((g * (Hxp / kw) + kx / kw) * nk + c) * R + r) * kw + kx % kw;
+}
+
 // The folded spectral kernel read from global memory: component c at the
 // folded indices (kyf, kzf) of column col.
-template <typename T, bool O32>
+template <typename T, int L, int AXIS, int NK>
 struct KGlobal {
-    using I = typename std::conditional<O32, unsigned, long>::type;
     const T* __restrict__ K;
-    I Kn, plane, Hxp, col;
+    int Hxp, col;
     __device__ __forceinline__ T operator()(int c, int kyf, int kzf) const
     {
-        return elem<O32>(K, (I)c * Kn + (I)kzf * plane + (I)kyf * Hxp + col);
+        constexpr int KW = mid_kw(sizeof(T), L), R = L / 2 + 1;
+        const long g = AXIS == 2 ? kyf : 0;
+        const int r = AXIS == 2 ? kzf : kyf;
+        return K[(((g * (Hxp / KW) + col / KW) * NK + c) * R + r) * KW + col % KW];
     }
 };
 
@@ -596,7 +622,7 @@ __device__ __forceinline__ void mid_group(cx<T> (&v)[3][G::kE], cx<T>* S, long o
 template <typename T, int L, int AXIS, bool HALF, bool O32, bool ADJ, int PROD = 0>
 __global__ __launch_bounds__((Mid<T, L>::kB * Mid<T, L>::kT)) void k_mid(
     cx<T>* S, const T* __restrict__ Khat, int n_valid, long es, long cs, long gstride, int ncols,
-    int ntile, long nblocks, int Py, int Pz, long Kn, int Hxp, const cx<T>* __restrict__ tw,
+    int ntile, long nblocks, int Py, int Pz, int Hxp, const cx<T>* __restrict__ tw,
     int Lmax)
 {
     using G = Mid<T, L>;
@@ -622,8 +648,7 @@ __global__ __launch_bounds__((Mid<T, L>::kB * Mid<T, L>::kT)) void k_mid(
     const int b = threadIdx.x % kB, t = threadIdx.x / kB;
     const int col = tile * kB + b;
     const bool cv = col < ncols;
-    using I = typename KGlobal<T, O32>::I;
-    const KGlobal<T, O32> kg{Khat, (I)Kn, (I)((long)(Py / 2 + 1) * Hxp), (I)Hxp, (I)col};
+    const KGlobal<T, L, AXIS, PROD == 0 ? 6 : 3> kg{Khat, Hxp, col};
     {
         cx<T> v[3][G::kE];
         mid_load<G, T, HALF, O32>(v, S, (long)g * gstride + col, n_valid, es, cs, cv, t);
@@ -655,16 +680,15 @@ struct MidW {
     static constexpr int kW = 2;  // AXIS = 2: the wavefronts of ky and Py - ky
 };
 
-// The block's folded kernel tile staged in LDS: component c at the folded
-// index r along the transform axis (kzf for AXIS = 2, kyf for AXIS = 1) of
-// column b of the tile, at t[(c * R + r) * CB + b].
-template <typename T, int AXIS, int R, int CB>
+// The block's folded kernel tile staged in LDS in the kernel's own layout:
+// component c at the folded index r along the transform axis (kzf for AXIS =
+// 2, kyf for AXIS = 1); t points to the thread's column.
+template <typename T, int AXIS, int R, int KW>
 struct KLds {
     const T* t;
-    int b;
     __device__ __forceinline__ T operator()(int c, int kyf, int kzf) const
     {
-        return t[(c * R + (AXIS == 2 ? kzf : kyf)) * CB + b];
+        return t[(c * R + (AXIS == 2 ? kzf : kyf)) * KW];
     }
 };
 
@@ -682,7 +706,7 @@ struct KLds {
 template <typename T, int L, int AXIS, bool HALF, bool O32, int PROD>
 __global__ __launch_bounds__((64 * MidW<T, L>::kW)) MMX_MIDW_ATTR void k_mid_w(
     cx<T>* S, const T* __restrict__ Khat, int n_valid, long es, long cs, long gstride, int ncols,
-    int ntb, long nblocks, int Py, int Pz, long Kn, int Hxp, const cx<T>* __restrict__ tw,
+    int ntb, long nblocks, int Py, int Pz, int Hxp, const cx<T>* __restrict__ tw,
     int Lmax, int nbatch, long bstride)
 {
     using G = MidW<T, L>;
@@ -691,7 +715,12 @@ __global__ __launch_bounds__((64 * MidW<T, L>::kW)) MMX_MIDW_ATTR void k_mid_w(
     constexpr int R = L / 2 + 1;                  // folded rows along the transform axis
     constexpr int NT = AXIS == 2 ? 1 : kW;        // column tiles per block
     constexpr int KT = NK * R * kCB;              // kernel values per tile
-    __shared__ T kt[NT * KT];
+    constexpr int KW = mid_kw(sizeof(T), L), KTW = NK * R * KW;
+    // values per load: up to 16 bytes that tiles are whole multiples of
+    constexpr int KV = KTW % 4 == 0 && sizeof(T) == 4 ? 4 : KTW % 2 == 0 ? 2 : 1;
+    static_assert(kCB % KW == 0, "whole kernel tiles per column tile");
+    typedef T KVec __attribute__((ext_vector_type(KV)));
+    __shared__ __attribute__((aligned(16))) T kt[NT * KT];
     __shared__ cx<T> twl[L];
     __shared__ cx<T> lds[kW][G::S::kStages > 1 ? kCB * G::S::kLds : 1];
     long lb = xcd_logical();
@@ -723,29 +752,17 @@ __global__ __launch_bounds__((64 * MidW<T, L>::kW)) MMX_MIDW_ATTR void k_mid_w(
     const bool cv = active && col < ncols;
     // one memory phase: the kernel tile(s) and twiddles for LDS, then the
     // spectrum column (every thread of the block takes part in the staging).
-    // Staging: thread (rr, bb) = (tid / kCB, tid % kCB) takes rows rr, rr + RCH,
-    // ... of every component; offsets other than its own are uniform.
-    using I = typename std::conditional<O32, unsigned, long>::type;
-    const I plane = (I)(Py / 2 + 1) * (I)Hxp;
-    constexpr int RCH = 64 * kW / kCB;              // rows per staging round
-    constexpr int NCH = (R + RCH - 1) / RCH;         // rounds per component
-    constexpr int NQ = NT * NK * NCH;
+    // Staging: the block's kernel values are contiguous (mid_index).
+    constexpr int NQ = (NT * KT / KV + 64 * kW - 1) / (64 * kW);
     constexpr int NTW = (L + 64 * kW - 1) / (64 * kW);
-    const int rr = (int)threadIdx.x / kCB, bb = (int)threadIdx.x % kCB;
-    T kv[NQ];
+    const long ktile = (long)tile0 * (kCB / KW), ktiles = Hxp / KW;
+    const T* Kb = Khat + ((AXIS == 2 ? gp : 0) * ktiles + ktile) * KTW;
+    const int kend = (int)((ktiles - ktile < NT * (kCB / KW) ? ktiles - ktile : NT * (kCB / KW)) * KTW);
+    KVec kv[NQ];
 #pragma unroll
-    for (int tl = 0; tl < NT; ++tl) {
-        const int cl = (tile0 + tl) * kCB + bb;
-        const I base = (AXIS == 2 ? (I)rr * plane + (I)gp * (I)Hxp : (I)rr * (I)Hxp) + (I)cl;
-        const I rstep = AXIS == 2 ? (I)RCH * plane : (I)RCH * (I)Hxp;
-#pragma unroll
-        for (int c = 0; c < NK; ++c)
-#pragma unroll
-            for (int ch = 0; ch < NCH; ++ch) {
-                const bool use = cl < ncols && ch * RCH + rr < R;
-                kv[(tl * NK + c) * NCH + ch] =
-                    use ? elem<O32>(Khat, base + (I)c * (I)Kn + (I)ch * rstep) : (T)0;
-            }
+    for (int q = 0; q < NQ; ++q) {
+        const int i = (q * 64 * kW + (int)threadIdx.x) * KV;
+        kv[q] = i < kend ? *reinterpret_cast<const KVec*>(Kb + i) : KVec(0);
     }
     const int tws = Lmax / L;
     cx<T> twv[NTW];
@@ -757,14 +774,10 @@ __global__ __launch_bounds__((64 * MidW<T, L>::kW)) MMX_MIDW_ATTR void k_mid_w(
     cx<T> v[3][G::kE];
     mid_load<G, T, HALF, O32>(v, S, (long)g * gstride + col, n_valid, es, cs, cv, t);
 #pragma unroll
-    for (int tl = 0; tl < NT; ++tl)
-#pragma unroll
-        for (int c = 0; c < NK; ++c)
-#pragma unroll
-            for (int ch = 0; ch < NCH; ++ch)
-                if (ch * RCH + rr < R)
-                    kt[tl * KT + (c * R + ch * RCH) * kCB + (int)threadIdx.x] =
-                        kv[(tl * NK + c) * NCH + ch];
+    for (int q = 0; q < NQ; ++q) {
+        const int i = (q * 64 * kW + (int)threadIdx.x) * KV;
+        if (i < NT * KT) *reinterpret_cast<KVec*>(kt + i) = kv[q];
+    }
 #pragma unroll
     for (int q = 0; q < NTW; ++q) {
         const int n = q * 64 * kW + (int)threadIdx.x;
@@ -772,7 +785,7 @@ __global__ __launch_bounds__((64 * MidW<T, L>::kW)) MMX_MIDW_ATTR void k_mid_w(
     }
     __syncthreads();
     if (!active || tile * kCB >= ncols) return;  // from here on, no workgroup barrier
-    const KLds<T, AXIS, R, kCB> kg{kt + (AXIS == 2 ? 0 : wave * KT), b};
+    const KLds<T, AXIS, R, KW> kg{kt + (AXIS == 2 ? 0 : wave * KT) + b / KW * KTW + b % KW};
     mid_group<G, true, T, L, AXIS, HALF, O32, PROD>(v, S, (long)g * gstride + col, kg, n_valid,
                                                     es, cs, cv, g, t, lds[wave] + b, kCB, Py, Pz,
                                                     twl, 1);
@@ -1719,20 +1732,19 @@ static hipError_t launch_mid_L(const Plan& p, cx<T>* S, int n_valid, long es, lo
 {
     // AXIS = 2 pairs ky with Py - ky: groups 0 .. Py/2
     const int groups = (AXIS == 2 && G > 1) ? G / 2 + 1 : G;
-    const bool o32 = (size_t)p.S2n * 2 * sizeof(T) < (1ull << 32) &&
-                     (size_t)p.Kn * 6 * sizeof(T) < (1ull << 32);
+    const bool o32 = (size_t)p.S2n * 2 * sizeof(T) < (1ull << 32);
     const bool half = 2 * n_valid <= L && L > 1;
     if constexpr (MMX_MIDW && MidW<T, L>::kOK) {
         using Gw = MidW<T, L>;
-        const int ntile = (p.Hx + Gw::kCB - 1) / Gw::kCB;
+        const int ntile = (p.Hc + Gw::kCB - 1) / Gw::kCB;
         const int ntb = ntile;
         const long nb = AXIS == 2 ? (long)ntb * groups : (ntile + Gw::kW - 1) / Gw::kW;
         // a batch: the requests' spectra follow each other, 3 components apart
         const int nbatch = p.batch > 1 ? p.batch : 1;
 #define MMX_KMIDW(H, O)                                                                           \
     k_mid_w<T, L, AXIS, H, O, PROD><<<xcd_grid(nb * nbatch), 64 * Gw::kW, 0, p.stream>>>(         \
-        S, (const T*)p.Khat, n_valid, es, cs, gstride, p.Hx, ntb, nb, p.P[1], p.P[2], p.Kn,       \
-        p.Hxp, (const cx<T>*)p.tw, p.Lmax, nbatch, 3 * cs)
+        S, (const T*)p.Khat, n_valid, es, cs, gstride, p.Hc, ntb, nb, p.P[1], p.P[2], p.Hxp,     \
+        (const cx<T>*)p.tw, p.Lmax, nbatch, 3 * cs)
         if (half && o32)
             MMX_KMIDW(true, true);
         else if (half)
@@ -1746,7 +1758,7 @@ static hipError_t launch_mid_L(const Plan& p, cx<T>* S, int n_valid, long es, lo
     } else {
     if (p.batch > 1) return hipErrorInvalidValue;  // batches need the wave-local kernel
     using Gm = Mid<T, L>;
-    const int ntile = (p.Hx + Gm::kB - 1) / Gm::kB;
+    const int ntile = (p.Hc + Gm::kB - 1) / Gm::kB;
     const long nblocks = (long)ntile * groups;
     // the Oersted product (PROD 1) uses the paired-in-block order only
     const bool adj = PROD == 0 && (sizeof(T) == 4 ? MMX_MID_ADJ_F32 : MMX_MID_ADJ_F64) &&
@@ -1754,8 +1766,8 @@ static hipError_t launch_mid_L(const Plan& p, cx<T>* S, int n_valid, long es, lo
     const long nb = adj ? 2 * nblocks : nblocks;
 #define MMX_KMID(H, O, AD)                                                                        \
     k_mid<T, L, AXIS, H, O, AD, PROD><<<xcd_grid(nb), Gm::kB * Gm::kT, 0, p.stream>>>(            \
-        S, (const T*)p.Khat, n_valid, es, cs, gstride, p.Hx, ntile, nb, p.P[1], p.P[2], p.Kn,     \
-        p.Hxp, (const cx<T>*)p.tw, p.Lmax)
+        S, (const T*)p.Khat, n_valid, es, cs, gstride, p.Hc, ntile, nb, p.P[1], p.P[2], p.Hxp,   \
+        (const cx<T>*)p.tw, p.Lmax)
 #define MMX_KMID2(H, O)                  \
     if constexpr (PROD == 0) {           \
         if (adj)                         \
