@@ -590,7 +590,10 @@ mm_status plan_build(const int grid[3], const double cell[3], double Ms, double 
     p->Kn = p->layered ? (long)grid[2] * (grid[2] + 1) / 2 * (p->P[1] / 2 + 1) * p->Hxp
                        : (long)(p->P[2] / 2 + 1) * (p->P[1] / 2 + 1) * p->Hxp;
     p->Lmax = std::max(p->P[0], std::max(p->P[1], p->P[2]));
-    p->plane = !p->layered && plane_shape(o.prec, p->P[0], p->P[1], p->P[2]);
+    // (a single layer keeps the plane path's spectrum in S1, which a few long
+    // rows overfill)
+    p->plane = !p->layered && plane_shape(o.prec, p->n, p->P) &&
+               (p->P[2] > 1 || (long)(p->P[0] / 2) * ((grid[1] + 1) & ~1) <= (long)grid[1] * p->Hxp);
     p->prec = o.prec;
     p->Ms = Ms;
     p->A = A;

@@ -149,8 +149,8 @@ hipError_t prof_flush(Plan &p);
 // Thread-local error message (mm_last_error).
 void set_error(const std::string &msg);
 
-// Whether the one-kernel y/z passes cover these padded extents.
-bool plane_shape(int prec, int Px, int Py, int Pz);
+// Whether a grid n (padded extents P) runs its y and z passes in one kernel.
+bool plane_shape(int prec, const int n[3], const int P[3]);
 
 // Device pipeline, instantiated for float and double in kernels.hip.
 template <typename T>

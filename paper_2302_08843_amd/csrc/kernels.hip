@@ -589,7 +589,6 @@ struct AdjParams {
     long s1_comp;
     int Hxp;
     int with_demag, with_exch, with_anis;
-    int tr;       // transposed spectrum (plane plans)
     double Ms;
     double exch;  // 2 A / mu0
     double idx2, idy2, idz2;
@@ -597,93 +596,138 @@ struct AdjParams {
     double eu[3];
 };
 
-// nu = g + H^T z (x inverse transform of the spectrum of K z in S1, then the
-// transposed local terms); gms += d(z.h)/dMs (double, may be null).
-template <typename T, int M, bool PERCELL>
-__global__ __launch_bounds__((XC2R<T, M>::kRows * 3 * XC2R<T, M>::kT)) void k_adj_local(
+// nu = g + H^T z at one cell, with kz the demag convolution of z there (the x
+// inverse transform) and zc, mc, msc: z, m and Ms of the cell (0) and its six
+// neighbours (x -+, y -+, z -+; an absent one holds the cell itself, has
+// false); *dms: d(z.h)/dMs.
+template <typename T>
+__device__ __forceinline__ void adj_cell(const AdjParams& P, const T (&kz)[3], const T (&g)[3],
+                                         const T (&zc)[7][3], const T (&mc)[7][3],
+                                         const T (&msc)[7], const bool (&has)[6], T (&nu)[3],
+                                         double* dms)
+{
+    const T ms = msc[0];
+    const T w3[3] = {(T)P.idx2, (T)P.idy2, (T)P.idz2};
+    double d = 0.0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) nu[c] = g[c];
+    if (P.with_demag) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) nu[c] += ms * kz[c];
+        d += (double)mc[0][0] * kz[0] + (double)mc[0][1] * kz[1] + (double)mc[0][2] * kz[2];
+    }
+    if (ms != (T)0) {
+        const T inv_ms = (T)1 / ms;
+        const T* z = zc[0];
+        if (P.with_exch) {
+            // A~ (z / Ms) and A~ m over magnetic neighbours
+            const T exch = (T)P.exch;
+            T a[3] = {0, 0, 0}, l[3] = {0, 0, 0};
+#pragma unroll
+            for (int n = 0; n < 6; ++n) {
+                const bool ok = has[n] && msc[n + 1] != (T)0;
+                const T w = ok ? w3[n >> 1] : (T)0, iq = ok ? (T)1 / msc[n + 1] : (T)0;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    a[c] += w * (zc[n + 1][c] * iq - z[c] * inv_ms);
+                    l[c] += w * (mc[n + 1][c] - mc[0][c]);
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < 3; ++c) nu[c] += exch * a[c];
+            d -= (double)(exch * inv_ms * inv_ms) *
+                 ((double)z[0] * l[0] + (double)z[1] * l[1] + (double)z[2] * l[2]);
+        }
+        if (P.with_anis) {
+            const T e[3] = {(T)P.eu[0], (T)P.eu[1], (T)P.eu[2]}, anis = (T)P.anis;
+            const T ez = e[0] * z[0] + e[1] * z[1] + e[2] * z[2];
+            const T em = e[0] * mc[0][0] + e[1] * mc[0][1] + e[2] * mc[0][2];
+            const T ca = anis * inv_ms * ez;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) nu[c] += ca * e[c];
+            d -= (double)(anis * inv_ms * inv_ms) * (double)ez * (double)em;
+        }
+    }
+    *dms = d;
+}
+
+// nu = g + H^T z (x inverse transform of the spectrum of K z, then the
+// transposed local terms); gms += d(z.h)/dMs (double, may be null).  The
+// block shape, the wave-local transforms and the loads of cells and
+// neighbours ahead of them are those of the local pass: at 128x128x1 FP32 7.6 us
+// instead of the 19 of a version that transformed with block barriers and read
+// its neighbours one by one.  XFORM false (a single cell along x): the
+// spectrum is the field.
+template <typename T, int M, bool TR, bool PERCELL, bool XFORM>
+__global__ __launch_bounds__((XFORM ? XC2RW<T, M, TR>::kNT : 256)) void k_adj_local(
     const cx<T>* __restrict__ S1, const T* __restrict__ m, const T* __restrict__ z,
     const T* __restrict__ g, const T* __restrict__ Ms_cell, AdjParams P, T* __restrict__ nu,
-    double* __restrict__ gms, int njt, long nblocks, const cx<T>* __restrict__ tw, int Lmax)
+    double* __restrict__ gms, long nblocks, const cx<T>* __restrict__ tw, int Lmax)
 {
-    using G = XC2R<T, M>;
-    constexpr int kRows = G::kRows, kL = G::kL;
-    __shared__ cx<T> lds[kRows * 3 * kL];
+    using G = XC2RW<T, M, TR>;
+    constexpr int NT = XFORM ? G::kNT : 256, RB = XFORM ? G::kRB : 256;
+    constexpr int CPT = XFORM ? G::kCPT : 1, LM = XFORM ? G::kLogM : 0, kL = XFORM ? G::kL : 1;
+    __shared__ cx<T> lds[XFORM ? 3 * RB * kL : 1];
+    __shared__ cx<T> twl[XFORM ? M : 1];
     const long lb = xcd_logical();
     if (lb >= nblocks) return;
-    const int k = MMX_X1_KFAST ? (int)(lb % P.nz) : (int)(lb / njt);
-    const int j0 = (MMX_X1_KFAST ? (int)(lb / P.nz) : (int)(lb % njt)) * kRows;
-    const int nx = P.nx, ny = P.ny;
-    if (P.with_demag) {
-        if (P.tr)
-            x_c2r_rows<T, M, true>(S1, lds, k, j0, ny, P.s1_comp, P.Hxp, tw, Lmax, P.nz);
-        else
-            x_c2r_rows<T, M>(S1, lds, k, j0, ny, P.s1_comp, P.Hxp, tw, Lmax);
+    const int nx = P.nx, ny = P.ny, nz = P.nz, tid = threadIdx.x;
+    const int k = (int)((unsigned)lb % (unsigned)nz);
+    const int j0 = (int)((unsigned)lb / (unsigned)nz) * RB;
+    const bool demag = P.with_demag != 0;
+    XInvW<T, XFORM ? M : 2, TR> xi;
+    if constexpr (XFORM) xi.load(S1, P.s1_comp, P.Hxp, k, j0, ny, nz, demag, tw, Lmax);
+    const long N = P.N, sxy = (long)nx * ny;
+    bool cv[CPT], has[CPT][6];
+    long cell[CPT];
+    T zc[CPT][7][3], mc[CPT][7][3], msc[CPT][7], gc[CPT][3];
+    double g0[CPT];
+#pragma unroll
+    for (int q = 0; q < CPT; ++q) {
+        const int li = tid + NT * q, rl = li >> LM, i = li & ((1 << LM) - 1), j = j0 + rl;
+        cv[q] = rl < RB && i < nx && j < ny;
+        const long c0 = cv[q] ? i + (long)nx * j + sxy * k : 0;
+        cell[q] = c0;
+        has[q][0] = cv[q] && i > 0;
+        has[q][1] = cv[q] && i + 1 < nx;
+        has[q][2] = cv[q] && j > 0;
+        has[q][3] = cv[q] && j + 1 < ny;
+        has[q][4] = cv[q] && k > 0;
+        has[q][5] = cv[q] && k + 1 < nz;
+        const long off[3] = {1, nx, sxy};
+#pragma unroll
+        for (int d = 0; d < 7; ++d) {
+            const long qq = d == 0 || !has[q][d - 1] ? c0 : (d & 1) ? c0 - off[(d - 1) >> 1] : c0 + off[(d - 1) >> 1];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                zc[q][d][c] = z[c * N + qq];
+                mc[q][d][c] = m[c * N + qq];
+            }
+            msc[q][d] = PERCELL ? Ms_cell[qq] : (T)P.Ms;
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) gc[q][c] = g ? g[c * N + c0] : (T)0;
+        g0[q] = gms ? gms[c0] : 0.0;
     }
-    const long N = P.N;
-    const T exch = (T)P.exch, anis = (T)P.anis;
-    const T ix2 = (T)P.idx2, iy2 = (T)P.idy2, iz2 = (T)P.idz2;
-    const T eux = (T)P.eu[0], euy = (T)P.eu[1], euz = (T)P.eu[2];
-    for (int idx = threadIdx.x; idx < kRows * nx; idx += blockDim.x) {
-        const int rl = idx / nx, i = idx - rl * nx;
-        const int j = j0 + rl;
-        if (j >= ny) continue;
-        const long cell = i + (long)nx * (j + (long)ny * k);
-        const T ms = PERCELL ? Ms_cell[cell] : (T)P.Ms;
-        const T mx = m[cell], my = m[N + cell], mz = m[2 * N + cell];
-        T nx_ = g ? g[cell] : (T)0, ny_ = g ? g[N + cell] : (T)0, nz_ = g ? g[2 * N + cell] : (T)0;
-        double dms = 0.0;
-        if (P.with_demag) {
-            const T kx = x_c2r_value<T, M>(S1, lds, rl, 0, i, k, j, ny, P.s1_comp, P.Hxp);
-            const T ky = x_c2r_value<T, M>(S1, lds, rl, 1, i, k, j, ny, P.s1_comp, P.Hxp);
-            const T kz = x_c2r_value<T, M>(S1, lds, rl, 2, i, k, j, ny, P.s1_comp, P.Hxp);
-            nx_ += ms * kx;
-            ny_ += ms * ky;
-            nz_ += ms * kz;
-            dms += (double)mx * kx + (double)my * ky + (double)mz * kz;
-        }
-        if (ms != (T)0) {
-            const T inv_ms = (T)1 / ms;
-            const T zx = z[cell], zy = z[N + cell], zz = z[2 * N + cell];
-            if (P.with_exch) {
-                // A~ (z / Ms) and A~ m over magnetic neighbours
-                T ax = 0, ay = 0, az = 0, lx = 0, ly = 0, lz = 0;
-                const T szx = zx * inv_ms, szy = zy * inv_ms, szz = zz * inv_ms;
-                auto nb = [&](long q, T w) {
-                    const T mq = PERCELL ? Ms_cell[q] : (T)P.Ms;
-                    if (mq == (T)0) return;
-                    const T iq = (T)1 / mq;
-                    ax += w * (z[q] * iq - szx);
-                    ay += w * (z[N + q] * iq - szy);
-                    az += w * (z[2 * N + q] * iq - szz);
-                    lx += w * (m[q] - mx);
-                    ly += w * (m[N + q] - my);
-                    lz += w * (m[2 * N + q] - mz);
-                };
-                if (i > 0) nb(cell - 1, ix2);
-                if (i + 1 < nx) nb(cell + 1, ix2);
-                if (j > 0) nb(cell - nx, iy2);
-                if (j + 1 < ny) nb(cell + nx, iy2);
-                if (k > 0) nb(cell - (long)nx * ny, iz2);
-                if (k + 1 < P.nz) nb(cell + (long)nx * ny, iz2);
-                nx_ += exch * ax;
-                ny_ += exch * ay;
-                nz_ += exch * az;
-                dms -= (double)(exch * inv_ms * inv_ms) * ((double)zx * lx + (double)zy * ly + (double)zz * lz);
-            }
-            if (P.with_anis) {
-                const T ez = eux * zx + euy * zy + euz * zz;
-                const T em = eux * mx + euy * my + euz * mz;
-                const T ca = anis * inv_ms * ez;
-                nx_ += ca * eux;
-                ny_ += ca * euy;
-                nz_ += ca * euz;
-                dms -= (double)(anis * inv_ms * inv_ms) * (double)ez * (double)em;
+    if constexpr (XFORM) xi.transform(lds, twl, demag, tw, Lmax);
+#pragma unroll
+    for (int q = 0; q < CPT; ++q) {
+        if (!cv[q]) continue;
+        const int li = tid + NT * q, rl = li >> LM, i = li & ((1 << LM) - 1);
+        T kz[3] = {0, 0, 0}, out[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            if constexpr (XFORM) {
+                if (demag) kz[c] = reinterpret_cast<const T*>(lds + (rl * 3 + c) * kL)[i];
+            } else {
+                if (demag) kz[c] = S1[c * P.s1_comp + ((long)k * ny + j0 + rl) * P.Hxp].x;
             }
         }
-        nu[cell] = nx_;
-        nu[N + cell] = ny_;
-        nu[2 * N + cell] = nz_;
-        if (gms) gms[cell] += dms;
+        double dms;
+        adj_cell(P, kz, gc[q], zc[q], mc[q], msc[q], has[q], out, &dms);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) nu[c * N + cell[q]] = out[c];
+        if (gms) gms[cell[q]] = g0[q] + dms;
     }
 }
 
@@ -748,17 +792,29 @@ __global__ void k_zero_d(double* __restrict__ p, long n)
         p[q] = 0.0;
 }
 
+template <typename T, int M, bool PC, bool TR>
+static hipError_t launch_adj_W(const Plan& p, const T* m, const T* z, const T* g, T* nu,
+                               double* gms, const AdjParams& P)
+{
+    constexpr bool XF = M >= 2;
+    using G = XC2RW<T, M, TR>;
+    const int rb = XF ? G::kRB : 256;
+    const long nblocks = (long)((p.n[1] + rb - 1) / rb) * p.n[2];
+    k_adj_local<T, M, TR, PC, XF><<<xcd_grid(nblocks), XF ? G::kNT : 256, 0, p.stream>>>(
+        (const cx<T>*)(TR ? p.S2 : p.S1), m, z, g, (const T*)p.Ms_cell, P, nu, gms, nblocks,
+        (const cx<T>*)p.tw, p.Lmax);
+    return hipGetLastError();
+}
+
 template <typename T, int M, bool PC>
 static hipError_t launch_adj_M(const Plan& p, const T* m, const T* z, const T* g, T* nu,
                                double* gms, const AdjParams& P)
 {
-    using G = XC2R<T, M>;
-    const int njt = (p.n[1] + G::kRows - 1) / G::kRows;
-    const long nblocks = (long)njt * p.n[2];
-    k_adj_local<T, M, PC><<<xcd_grid(nblocks), G::kRows * 3 * G::kT, 0, p.stream>>>(
-        (const cx<T>*)(p.plane ? p.S2 : p.S1), m, z, g, (const T*)p.Ms_cell, P, nu, gms, njt, nblocks,
-        (const cx<T>*)p.tw, p.Lmax);
-    return hipGetLastError();
+    if constexpr (M >= 2 && XC2RW<T, M>::kOK)
+        if (p.plane) return launch_adj_W<T, M, PC, true>(p, m, z, g, nu, gms, P);
+    if constexpr (M < 2 || XC2RW<T, M>::kOK)
+        return launch_adj_W<T, M, PC, false>(p, m, z, g, nu, gms, P);
+    return hipErrorInvalidValue;
 }
 
 template <typename T, bool PC>
@@ -879,20 +935,26 @@ __global__ void k_fold_plane(T* __restrict__ Khat, const cx<double>* __restrict_
 // with both q at once in FP32 from 32 columns on (8x512x4: 34 against 32,
 // 31x221x3: 25 against 34).  Many columns of very few rows or of deep stacks
 // make many short blocks (512x5x3: 22 against 21, 512x20x20: 56 against 54).
+// One q after the other also needs a plane that is mostly cells, since it
+// transforms the layers and rows up to the powers of two (416x314x6: 128
+// against 123).  A single layer in FP64 with rows of 1024 gains from the plane
+// kernel less than it loses in the x passes until there are many rows
+// (500x30x1: 21.4 against 20.1, 512x512x1: 46 against 64).
 template <typename G>
-static bool plane_pays(int prec, int Px, int Py, int Pz)
+static bool plane_pays(int prec, const int n[3], const int P[3])
 {
-    if (Px < 4 || (Px >= 1024 && (Py <= 16 || Pz >= 64))) return false;
-    if (prec == MM_FP64 && G::kBytes > 80 * 1024) return Px >= 512;
-    if (G::kNT == G::kNTQ) return Px >= 512;
-    return G::kBytes <= 80 * 1024 || Px >= 64;
+    if (P[0] < 4 || (P[0] >= 1024 && (P[1] <= 16 || P[2] >= 64))) return false;
+    if (prec == MM_FP64 && P[0] >= 1024 && P[2] == 1 && P[1] < 512) return false;
+    if (prec == MM_FP64 && G::kBytes > 80 * 1024) return P[0] >= 512;
+    if (G::kNT == G::kNTQ) return P[0] >= 512 && 8L * n[1] * n[2] >= (long)P[1] * P[2];
+    return G::kBytes <= 80 * 1024 || P[0] >= 64;
 }
 
-bool plane_shape(int prec, int Px, int Py, int Pz)
+bool plane_shape(int prec, const int n[3], const int P[3])
 {
 #define MMX_PLANE_HAS(T, YP, EY, PZ, LZ, NQ, NTQ) \
-    if (Py == 2 * YP && Pz == PZ)                 \
-        return plane_pays<PlaneG<T, YP, EY, PZ, LZ, NQ, NTQ>>(prec, Px, Py, Pz);
+    if (P[1] == 2 * YP && P[2] == PZ)             \
+        return plane_pays<PlaneG<T, YP, EY, PZ, LZ, NQ, NTQ>>(prec, n, P);
 #define MMX_PLANE_HAS32(YP, EY, PZ, LZ, NQ, NTQ) MMX_PLANE_HAS(float, YP, EY, PZ, LZ, NQ, NTQ)
 #define MMX_PLANE_HAS64(YP, EY, PZ, LZ, NQ, NTQ) MMX_PLANE_HAS(double, YP, EY, PZ, LZ, NQ, NTQ)
     if (prec == MM_FP32) {
@@ -1374,7 +1436,7 @@ static hipError_t demag_to_S1(Plan& p, const T* m, bool use_ms, const StageIn<T>
     if (p.Pb && (pc || !use_ms || sc || !p.Ms_b || M < 2)) return hipErrorInvalidValue;
     // plane plans keep the x spectrum transposed, in S2
     cx<T>* X = p.plane ? S2 : S1;
-    const long xc = p.plane ? p.S2n : s1c;
+    const long xc = p.plane ? plane_stride(p) : s1c;
     MMX_TRY(timed(p, MM_PASS_X_FWD, [&] {
         return pc ? launch_x_r2c<T, true>(p, M, m, nx, p.N, nx, (const T*)p.Ms_cell, ms, X, p.Hxp,
                                           xc, ny * nz, 3, sc, p.plane)
@@ -2066,7 +2128,6 @@ hipError_t field_vjp(Plan& p, const T* m, const T* w, const T* h, unsigned terms
     P.s1_comp = (long)p.n[2] * p.n[1] * p.Hxp;
     P.Hxp = p.Hxp;
     P.with_demag = demag ? 1 : 0;
-    P.tr = p.plane ? 1 : 0;
     P.with_exch = (terms & MM_EXCH) && p.A != 0.0 ? 1 : 0;
     P.with_anis = (terms & MM_ANIS) && p.Ku != 0.0 ? 1 : 0;
     P.Ms = p.Ms;

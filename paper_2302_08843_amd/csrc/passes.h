@@ -224,11 +224,14 @@ struct XR2C {
     using S = FFTShape<M, Regs<T>::x>;
     static constexpr int kE = S::kE, kT = S::kT;
     static constexpr int kRows =
-        TR ? (M >= 512 || sizeof(T) == 8 ? 8 : 16) : cmax(1, MMX_XBLOCK / kT);
+        TR ? (sizeof(T) == 8 ? (M >= 512 ? 4 : 8) : M >= 512 ? 8 : 16) : cmax(1, MMX_XBLOCK / kT);
     static constexpr int kL = TR ? (S::kLds + 31) / 32 * 32 + 2 : S::kLds;
 };
 // Row pitch of the transposed spectrum.
 __host__ __device__ constexpr int plane_pitch(int ny) { return (ny + 1) & ~1; }
+// Distance of two requests' transposed spectra: they live in S2, which is S1
+// for single layers.
+inline long plane_stride(const Plan& p) { return p.S2 == p.S1 ? p.S1n : p.S2n; }
 
 // COMB: the rows are those of a Runge-Kutta stage input y + sum_j c_j k_j
 // (StageIn; `in` is y), formed here in the order and precision of the
@@ -842,12 +845,11 @@ __device__ inline void atomic_max_nonneg(double* addr, double v)
 // as reals at lds + (rl*3 + c)*kL (x = 0 .. 2M-1, only x < M written).
 // 2M-point real inverse via an M-point complex inverse of
 //   2 Z[n] = (X[n] + conj X[M-n]) + i w^-n (X[n] - conj X[M-n]).
-// Contains barriers: every thread of the block must call it.  TR: S1 is the
-// transposed spectrum of plane plans (nz layers).
-template <typename T, int M, bool TR = false>
+// Contains barriers: every thread of the block must call it.
+template <typename T, int M>
 __device__ __forceinline__ void x_c2r_rows(const cx<T>* __restrict__ S1, cx<T>* lds, int k, int j0,
                                            int ny, long s1_comp, int Hxp,
-                                           const cx<T>* __restrict__ tw, int Lmax, int nz = 1)
+                                           const cx<T>* __restrict__ tw, int Lmax)
 {
     using G = XC2R<T, M>;
     if constexpr (M >= 2) {
@@ -857,10 +859,7 @@ __device__ __forceinline__ void x_c2r_rows(const cx<T>* __restrict__ S1, cx<T>* 
         const int rl = threadIdx.x / (3 * kT);
         const int j = j0 + rl;
         const bool valid = rl < kRows && j < ny;
-        const int nyp = plane_pitch(ny);
-        const cx<T>* X = S1 + (TR ? ((long)c * nz + k) * nyp + (valid ? j : 0)
-                                  : c * s1_comp + ((long)k * ny + (valid ? j : 0)) * Hxp);
-        const long xs = TR ? 3L * nz * nyp : 1;
+        const cx<T>* X = S1 + c * s1_comp + ((long)k * ny + (valid ? j : 0)) * Hxp;
         const int tws = Lmax / (2 * M);
         cx<T> v[kE];
 #pragma unroll
@@ -868,11 +867,7 @@ __device__ __forceinline__ void x_c2r_rows(const cx<T>* __restrict__ S1, cx<T>* 
             const int n = t + r * kT;
             cx<T> z = {0, 0};
             if (valid) {
-                cx<T> a = X[n * xs], bb = X[(TR ? (M - n) & (M - 1) : M - n) * xs];
-                if (TR && n == 0) {  // column 0 holds X_0 + i X_M
-                    bb = {a.y, (T)0};
-                    a.y = 0;
-                }
+                const cx<T> a = X[n], bb = X[M - n];
                 const cx<T> D = {a.x - bb.x, a.y + bb.y};
                 const cx<T> wD = cmulc(D, tw[n * tws]);
                 z = {a.x + bb.x - wD.y, a.y - bb.y + wD.x};
@@ -1170,6 +1165,120 @@ struct XC2RW {
     static_assert(!kOK || 3 * kRB * kT <= kNT, "transform threads exceed the block");
 };
 
+// The inverse x transforms of one block (rows j0 .. j0 + kRB - 1 of slab k,
+// three components): load() starts the spectrum and twiddle reads, transform()
+// leaves component c of row rl as reals at lds + (rl * 3 + c) * kL (x = 0 ..
+// M - 1); the caller's own loads go in between.  Every thread of the block
+// calls both; transform() ends with a barrier.
+template <typename T, int M, bool TR>
+struct XInvW {
+    using G = XC2RW<T, M, TR>;
+    static constexpr int kE = G::kE, kT = G::kT, RB = G::kRB, kL = G::kL;
+    static constexpr int NTW = (M + G::kNT - 1) / G::kNT;
+    // TR: pairs of rows (2 jp, 2 jp + 1) of (kx, component)
+    static constexpr int NPR = TR ? RB / 2 : 1;
+    static constexpr int NLD = TR ? (M * 3 * NPR + G::kNT - 1) / G::kNT : 1;
+    struct alignas(2 * sizeof(cx<T>)) cx2 {
+        cx<T> a, b;
+    };
+    cx<T> xa[TR ? 1 : kE], xb[TR ? 1 : kE];
+    cx2 xt[NLD];
+    cx<T> twv[NTW];
+
+    __device__ __forceinline__ void load(const cx<T>* __restrict__ S1, long s1_comp, int Hxp, int k,
+                                         int j0, int ny, int nz, bool with_demag,
+                                         const cx<T>* __restrict__ tw, int Lmax)
+    {
+        const int tid = threadIdx.x;
+        if constexpr (TR) {
+            const int nyp = plane_pitch(ny);
+            const unsigned o0 = (unsigned)(k * nyp + j0), oc = (unsigned)(nz * nyp);
+#pragma unroll
+            for (int q = 0; q < NLD; ++q) {
+                const int i = tid + G::kNT * q, jp = i % NPR, col = i / NPR;  // col = 3 kx + c
+                const bool use = with_demag && i < M * 3 * NPR && j0 + 2 * jp < ny;
+                xt[q] = use ? *reinterpret_cast<const cx2*>(
+                                  &elem<true>(S1, o0 + (unsigned)(2 * jp) + (unsigned)col * oc))
+                            : cx2{{0, 0}, {0, 0}};
+            }
+        } else {
+            const int tau = tid / kT, t = tid % kT, frl = tau / 3, fc = tau % 3;
+            const bool frow = with_demag && tid < 3 * RB * kT && j0 + frl < ny;
+            const cx<T>* X = S1 + (long)fc * s1_comp + ((long)k * ny + (frow ? j0 + frl : 0)) * Hxp;
+#pragma unroll
+            for (int r = 0; r < kE; ++r) {
+                const int n = t + r * kT;
+                xa[r] = frow ? X[n] : cx<T>{0, 0};
+                xb[r] = frow ? X[M - n] : cx<T>{0, 0};
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < NTW; ++q) {
+            const int n = tid + G::kNT * q;
+            twv[q] = n < M ? tw[n * (Lmax / M)] : cx<T>{0, 0};
+        }
+    }
+
+    __device__ __forceinline__ void transform(cx<T>* lds, cx<T>* twl, bool with_demag,
+                                              const cx<T>* __restrict__ tw, int Lmax)
+    {
+        const int tid = threadIdx.x;
+        const int tau = tid / kT, t = tid % kT, frl = tau / 3, fc = tau % 3;
+#pragma unroll
+        for (int q = 0; q < NTW; ++q) {
+            const int n = tid + G::kNT * q;
+            if (n < M) twl[n] = twv[q];
+        }
+        if constexpr (TR) {
+#pragma unroll
+            for (int q = 0; q < NLD; ++q) {
+                const int i = tid + G::kNT * q, jp = i % NPR, col = i / NPR;
+                if (i < M * 3 * NPR) {
+                    cx<T>* L = lds + (2 * jp * 3 + col % 3) * kL + col / 3;
+                    L[0] = xt[q].a;
+                    L[3 * kL] = xt[q].b;
+                }
+            }
+        }
+        __syncthreads();
+        cx<T>* X = lds + (frl * 3 + fc) * kL;
+        if (with_demag && tid < 3 * RB * kT) {
+            const int tws = Lmax / (2 * M);
+            cx<T> v[kE];
+#pragma unroll
+            for (int r = 0; r < kE; ++r) {
+                const int n = t + r * kT;
+                cx<T> a, bb;
+                if constexpr (TR) {
+                    a = X[n];
+                    bb = X[(M - n) & (M - 1)];
+                    if (n == 0) {  // column 0 holds X_0 + i X_M
+                        bb = {a.y, (T)0};
+                        a.y = 0;
+                    }
+                } else {
+                    a = xa[r];
+                    bb = xb[r];
+                }
+                const cx<T> D = {a.x - bb.x, a.y + bb.y};
+                const cx<T> wD = cmulc(D, tw[n * tws]);
+                v[r] = {a.x + bb.x - wD.y, a.y - bb.y + wD.x};
+            }
+            if constexpr (TR) fft_sync<true>();  // the reads above precede the first exchange
+            WgFFT<T, M, G::kRegs, 1, false, false, true>::run(v, t, X, 1, twl, 1);
+            fft_sync<true>();  // the transform's last exchange reads precede these writes
+            constexpr int Rl = G::S::kLast;
+#pragma unroll
+            for (int i = 0; i < kE; ++i) {
+                // outputs n >= M/2 are cells x >= M >= nx: never used
+                if ((i % Rl) >= Rl / 2) continue;
+                X[G::S::out_index(t, i)] = v[i];  // reals 2e, 2e + 1
+            }
+        }
+        __syncthreads();
+    }
+};
+
 // The error-norm accumulation of the last Dormand-Prince stage (ERR): the
 // partial error ep from the x forward pass, the state y, the coefficient e6
 // of the derivative computed here, the tolerances, and the block partials
@@ -1200,8 +1309,7 @@ __global__ __launch_bounds__((XC2RW<T, M, TR>::kNT)) void k_x_c2r_local_w(
     constexpr bool kDMI = EXT & EXT_DMI, kPA = EXT & EXT_PA, kPD = EXT & EXT_PD;
     constexpr bool kMIX = EXT & EXT_MIX, kLO = EXT & EXT_LO;
     using G = XC2RW<T, M, TR>;
-    constexpr int kE = G::kE, kT = G::kT, RB = G::kRB, CPT = G::kCPT, kL = G::kL;
-    constexpr int NTW = (M + G::kNT - 1) / G::kNT;
+    constexpr int RB = G::kRB, CPT = G::kCPT, kL = G::kL;
     __shared__ cx<T> lds[3 * RB * kL];
     __shared__ cx<T> twl[M];  // the M-point transform's twiddles
     long lb = xcd_logical();
@@ -1230,46 +1338,9 @@ __global__ __launch_bounds__((XC2RW<T, M, TR>::kNT)) void k_x_c2r_local_w(
     const unsigned N = (unsigned)Pk.N;
     const unsigned sxy = (unsigned)nx * (unsigned)ny;
 
-    // ---- memory phase: spectrum rows ----
     const bool with_demag = P.with_demag != 0;
-    const bool fthr = tid < 3 * RB * kT;
-    const int tau = tid / kT, t = tid % kT;
-    const int frl = tau / 3, fc = tau % 3;
-    const bool frow = with_demag && fthr && j0 + frl < ny;
-    cx<T> xa[TR ? 1 : kE], xb[TR ? 1 : kE];
-    // TR: pairs of rows (2 jp, 2 jp + 1) of (kx, component)
-    constexpr int NPR = TR ? RB / 2 : 1, NLD = TR ? (M * 3 * NPR + G::kNT - 1) / G::kNT : 1;
-    struct alignas(2 * sizeof(cx<T>)) cx2 {
-        cx<T> a, b;
-    };
-    cx2 xt[NLD];
-    if constexpr (TR) {
-        const int nyp = plane_pitch(ny);
-        const unsigned o0 = (unsigned)(k * nyp + j0), oc = (unsigned)(nz * nyp);
-#pragma unroll
-        for (int q = 0; q < NLD; ++q) {
-            const int i = tid + G::kNT * q, jp = i % NPR, col = i / NPR;  // col = 3 kx + c
-            const bool use = with_demag && i < M * 3 * NPR && j0 + 2 * jp < ny;
-            xt[q] = use ? *reinterpret_cast<const cx2*>(
-                              &elem<true>(S1, o0 + (unsigned)(2 * jp) + (unsigned)col * oc))
-                        : cx2{{0, 0}, {0, 0}};
-        }
-    } else {
-        const cx<T>* X =
-            S1 + (long)fc * Pk.s1_comp + ((long)k * ny + (frow ? j0 + frl : 0)) * Pk.Hxp;
-#pragma unroll
-        for (int r = 0; r < kE; ++r) {
-            const int n = t + r * kT;
-            xa[r] = frow ? X[n] : cx<T>{0, 0};
-            xb[r] = frow ? X[M - n] : cx<T>{0, 0};
-        }
-    }
-    cx<T> twv[NTW];
-#pragma unroll
-    for (int q = 0; q < NTW; ++q) {
-        const int n = tid + G::kNT * q;
-        twv[q] = n < M ? tw[n * (Lmax / M)] : cx<T>{0, 0};
-    }
+    XInvW<T, M, TR> xi;
+    xi.load(S1, Pk.s1_comp, Pk.Hxp, k, j0, ny, nz, with_demag, tw, Lmax);
     // ---- memory phase: cells and neighbours ----
     const T* mc0 = m;
     const T* mc1 = m + N;
@@ -1323,62 +1394,7 @@ __global__ __launch_bounds__((XC2RW<T, M, TR>::kNT)) void k_x_c2r_local_w(
         }
     }
 
-    // ---- inverse x transforms (three per row, each in one wavefront) ----
-#pragma unroll
-    for (int q = 0; q < NTW; ++q) {
-        const int n = tid + G::kNT * q;
-        if (n < M) twl[n] = twv[q];
-    }
-    if constexpr (TR) {
-#pragma unroll
-        for (int q = 0; q < NLD; ++q) {
-            const int i = tid + G::kNT * q, jp = i % NPR, col = i / NPR;
-            if (i < M * 3 * NPR) {
-                cx<T>* L = lds + (2 * jp * 3 + col % 3) * kL + col / 3;
-                L[0] = xt[q].a;
-                L[3 * kL] = xt[q].b;
-            }
-        }
-    }
-    __syncthreads();
-    T* hd = reinterpret_cast<T*>(lds + (frl * 3 + fc) * kL);
-    if (with_demag && fthr) {
-        const int tws = Lmax / (2 * M);
-        cx<T> v[kE];
-#pragma unroll
-        for (int r = 0; r < kE; ++r) {
-            const int n = t + r * kT;
-            cx<T> a, bb;
-            if constexpr (TR) {
-                const cx<T>* X = lds + (frl * 3 + fc) * kL;
-                a = X[n];
-                bb = X[(M - n) & (M - 1)];
-                if (n == 0) {  // column 0 holds X_0 + i X_M
-                    bb = {a.y, (T)0};
-                    a.y = 0;
-                }
-            } else {
-                a = xa[r];
-                bb = xb[r];
-            }
-            const cx<T> D = {a.x - bb.x, a.y + bb.y};
-            const cx<T> wD = cmulc(D, tw[n * tws]);
-            v[r] = {a.x + bb.x - wD.y, a.y - bb.y + wD.x};
-        }
-        if constexpr (TR) fft_sync<true>();  // the reads above precede the first exchange
-        WgFFT<T, M, G::kRegs, 1, false, false, true>::run(v, t, lds + (frl * 3 + fc) * kL, 1, twl,
-                                                          1);
-        fft_sync<true>();  // the transform's last exchange reads precede these writes
-        constexpr int Rl = G::S::kLast;
-#pragma unroll
-        for (int i = 0; i < kE; ++i) {
-            // outputs n >= M/2 are cells x >= M >= nx: never used
-            if ((i % Rl) >= Rl / 2) continue;
-            const int e = G::S::out_index(t, i);
-            reinterpret_cast<cx<T>*>(hd)[e] = v[i];  // reals 2e, 2e + 1
-        }
-    }
-    __syncthreads();
+    xi.transform(lds, twl, with_demag, tw, Lmax);
 
     // ---- local terms ----
     const T exch = (T)P.exch, anis = (T)P.anis;
@@ -1818,7 +1834,7 @@ static hipError_t launch_local_W(const Plan& p, const T* m, T* h, T* dm, const L
     if (nb_out) *nb_out = nblocks;
     const cx<T>* S = (const cx<T>*)(TR ? p.S2 : p.S1);
     const cx<T>* tw = (const cx<T>*)p.tw;
-    const long bstride = TR ? p.S2n : p.S1n;
+    const long bstride = TR ? plane_stride(p) : p.S1n;
     const LocalErr<T> no{};
     const T* none = nullptr;
     const T* h_oe = P.with_oe ? (const T*)p.h_oe : none;

@@ -89,7 +89,9 @@ __host__ __device__ inline int plane_kn(int q, int YP) { return YP / 2 + (q ? 0 
 // A field evaluation takes, before and after (us): FP32 64x64x2 27.4 / 16.1,
 // 128x128x2 32.3 / 19.3, 256x64x4 30.7 / 21.0, 256x256x8 60.4 / 48.3,
 // 256x256x16 107 / 91, 512x256x16 190 / 167; FP64 32x32x4 25.1 / 18.0,
-// 256x256x4 61.4 / 50.5, 256x256x8 92.3 / 80.1.  It is bound by VALU issue and
+// 256x256x4 61.4 / 50.5, 256x256x8 92.3 / 80.1.  Single layers, whose z pass
+// along y held 8 columns in one wavefront for 12 us at any small size: FP32
+// 64x64x1 21.0 / 15.0, 512x512x1 52.9 / 31.6; FP64 19.8 / 16.5, 63.7 / 45.6.  It is bound by VALU issue and
 // by the latency of its phases (a plane of 104 KB leaves one block per compute
 // unit, whose wavefronts meet at every barrier; VALUs busy about half of the
 // time), not by memory.  Hence as many threads as fit 128 registers without
@@ -459,25 +461,29 @@ __global__ __launch_bounds__((PlaneG<T, YP, EY, PZ, LZ, NQ, NTQ>::kNT)) void k_p
 
 // The shapes by padded y and z extents: MACRO(YP, EY, PZ, LZ, NQ, NTQ).
 #define MMX_PLANE_F32(X)                                                                    \
-    X(8, 4, 4, 1, 2, 8) X(8, 4, 8, 2, 2, 16) X(8, 4, 16, 2, 2, 16)                          \
-    X(8, 4, 32, 4, 2, 32) X(8, 4, 64, 8, 2, 64) X(16, 4, 4, 1, 2, 16)                       \
-    X(16, 4, 8, 2, 2, 32) X(16, 4, 16, 2, 2, 32) X(16, 4, 32, 4, 2, 64)                     \
-    X(16, 4, 64, 8, 2, 128) X(32, 8, 4, 1, 2, 32) X(32, 8, 8, 2, 2, 64)                     \
-    X(32, 8, 16, 2, 2, 64) X(32, 8, 32, 4, 2, 128) X(32, 8, 64, 8, 2, 256)                  \
+    X(8, 4, 1, 1, 2, 8) X(8, 4, 4, 1, 2, 8) X(8, 4, 8, 2, 2, 16) X(8, 4, 16, 2, 2, 16)      \
+    X(8, 4, 32, 4, 2, 32) X(8, 4, 64, 8, 2, 64) X(16, 4, 1, 1, 2, 16)                       \
+    X(16, 4, 4, 1, 2, 16) X(16, 4, 8, 2, 2, 32) X(16, 4, 16, 2, 2, 32)                      \
+    X(16, 4, 32, 4, 2, 64) X(16, 4, 64, 8, 2, 128) X(32, 8, 1, 1, 2, 32)                    \
+    X(32, 8, 4, 1, 2, 32) X(32, 8, 8, 2, 2, 64) X(32, 8, 16, 2, 2, 64)                      \
+    X(32, 8, 32, 4, 2, 128) X(32, 8, 64, 8, 2, 256) X(64, 8, 1, 1, 2, 64)                   \
     X(64, 8, 4, 1, 2, 64) X(64, 8, 8, 2, 2, 128) X(64, 8, 16, 2, 2, 128)                    \
-    X(64, 8, 32, 4, 2, 256) X(128, 16, 4, 1, 2, 128) X(128, 16, 8, 2, 2, 256)               \
-    X(128, 16, 16, 2, 2, 256) X(128, 16, 32, 4, 2, 512) X(256, 16, 4, 1, 2, 256)            \
-    X(256, 16, 8, 2, 2, 256) X(256, 16, 16, 2, 2, 512) X(256, 16, 32, 4, 1, 1024)           \
+    X(64, 8, 32, 4, 2, 256) X(128, 8, 1, 1, 2, 64) X(128, 16, 4, 1, 2, 128)                 \
+    X(128, 16, 8, 2, 2, 256) X(128, 16, 16, 2, 2, 256) X(128, 16, 32, 4, 2, 512)            \
+    X(256, 16, 1, 1, 2, 64) X(256, 16, 4, 1, 2, 256) X(256, 16, 8, 2, 2, 256)               \
+    X(256, 16, 16, 2, 2, 512) X(256, 16, 32, 4, 1, 1024) X(512, 16, 1, 1, 2, 128)           \
     X(512, 16, 4, 1, 2, 512) X(512, 16, 8, 2, 2, 256) X(512, 8, 16, 2, 1, 1024)
 #define MMX_PLANE_F64(X)                                                                    \
-    X(8, 4, 4, 1, 2, 8) X(8, 4, 8, 2, 2, 16) X(8, 4, 16, 4, 2, 32)                          \
-    X(8, 4, 32, 8, 2, 64) X(16, 4, 4, 1, 2, 16) X(16, 4, 8, 2, 2, 32)                       \
-    X(16, 4, 16, 4, 2, 64) X(16, 4, 32, 8, 2, 128) X(32, 8, 4, 1, 2, 32)                    \
-    X(32, 8, 8, 2, 2, 64) X(32, 8, 16, 2, 2, 64) X(32, 8, 32, 4, 2, 128)                    \
+    X(8, 4, 1, 1, 2, 8) X(8, 4, 4, 1, 2, 8) X(8, 4, 8, 2, 2, 16) X(8, 4, 16, 4, 2, 32)      \
+    X(8, 4, 32, 8, 2, 64) X(16, 4, 1, 1, 2, 16) X(16, 4, 4, 1, 2, 16)                       \
+    X(16, 4, 8, 2, 2, 32) X(16, 4, 16, 4, 2, 64) X(16, 4, 32, 8, 2, 128)                    \
+    X(32, 8, 1, 1, 2, 32) X(32, 8, 4, 1, 2, 32) X(32, 8, 8, 2, 2, 64)                       \
+    X(32, 8, 16, 2, 2, 64) X(32, 8, 32, 4, 2, 128) X(64, 8, 1, 1, 2, 64)                    \
     X(64, 8, 4, 1, 2, 64) X(64, 8, 8, 2, 2, 128) X(64, 8, 16, 2, 2, 128)                    \
-    X(64, 8, 32, 4, 2, 256) X(128, 8, 4, 1, 2, 128) X(128, 8, 8, 2, 2, 128)                 \
-    X(128, 8, 16, 2, 2, 256) X(128, 8, 32, 4, 1, 512) X(256, 8, 4, 1, 2, 256)               \
-    X(256, 8, 8, 2, 2, 256) X(256, 8, 16, 2, 1, 512) X(512, 8, 4, 1, 1, 512)                \
+    X(64, 8, 32, 4, 2, 256) X(128, 8, 1, 1, 2, 64) X(128, 8, 4, 1, 2, 128)                  \
+    X(128, 8, 8, 2, 2, 128) X(128, 8, 16, 2, 2, 256) X(128, 8, 32, 4, 1, 512)               \
+    X(256, 8, 1, 1, 2, 128) X(256, 8, 4, 1, 2, 256) X(256, 8, 8, 2, 2, 256)                 \
+    X(256, 8, 16, 2, 1, 512) X(512, 8, 1, 1, 2, 256) X(512, 8, 4, 1, 1, 512)                \
     X(512, 8, 8, 2, 1, 512)
 
 template <typename T>
@@ -495,7 +501,7 @@ hipError_t launch_plane<double>(const Plan& p);
         k_plane<MMX_PLANE_T, YP, EY, PZ, LZ, NQ, NTQ>                                        \
             <<<xcd_grid(nb), G::kNT, 0, p.stream>>>(                                         \
                 (V*)p.S2, (V*)p.S1, (const MMX_PLANE_T*)p.Khat, p.n[1], p.n[2],              \
-                plane_pitch(p.n[1]), M, nb, p.S2n, (const V*)p.tw, p.Lmax);                  \
+                plane_pitch(p.n[1]), M, nb, plane_stride(p), (const V*)p.tw, p.Lmax);                  \
         return hipGetLastError();                                                            \
     }
 

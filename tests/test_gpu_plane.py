@@ -16,10 +16,12 @@ pytestmark = pytest.mark.gpu
 
 BAR = {"fp64": 1e-12, "fp32": 2e-6}
 # smallest; LZ 1, 2, 4, 8; ny at YP and YP/2 + 1; packed columns with nx = 2;
-# NQ = 1 shapes; just outside (ny 4, nz 33, Px too small for a large plane)
+# NQ = 1 shapes; single layers (256, 5, 1: too large for the spectrum's place);
+# just outside (ny 4, nz 33, one cell along x, Px too small for a large plane)
 GRIDS = [(2, 5, 2), (3, 8, 2), (2, 9, 4), (5, 16, 3), (9, 17, 8), (33, 31, 5), (17, 24, 9),
          (12, 32, 16), (6, 33, 17), (10, 12, 31), (64, 65, 2), (40, 100, 7), (130, 129, 3),
          (32, 257, 2), (35, 300, 4), (257, 130, 9), (300, 260, 2), (512, 9, 2),
+         (2, 5, 1), (31, 64, 1), (65, 33, 1), (130, 257, 1), (300, 20, 1), (1, 9, 3), (256, 5, 1),
          (8, 4, 3), (12, 20, 33), (8, 300, 7)]
 
 
@@ -53,7 +55,7 @@ def test_field_and_transpose(mm, orc, grid, prec):
     plan.set_ms(Ms)
     h = to_np(plan.heff(m, None, mm.MM_DEMAG))
     assert rel_l2(h, o.heff(m, terms=orc.DEMAG)) <= BAR[prec]
-    gm, _ = plan.heff_vjp(m, w, mm.MM_DEMAG)
-    ref = o.heff_vjp(m, w, terms=orc.DEMAG)
-    ref = ref[0] if isinstance(ref, tuple) else ref
+    gm, gms = plan.heff_vjp(m, w, mm.MM_DEMAG)
+    ref, ref_ms = o.heff_vjp(m, w, terms=orc.DEMAG)
     assert rel_l2(to_np(gm), ref) <= BAR[prec]
+    assert rel_l2(to_np(gms), ref_ms) <= BAR[prec]
