@@ -185,6 +185,7 @@ struct StageIn {
     // like c_j), formed in double from the same loads and stored to ep
     T *ep = nullptr;
     double e[7] = {};
+    int mask = 0;  // set by the x forward pass
 };
 
 // The Dormand-Prince error norm accumulated by the local pass of the last
