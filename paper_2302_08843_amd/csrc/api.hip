@@ -225,7 +225,7 @@ static mm_status fetch(Plan* p, int n)
 static mm_status ensure_adj(Plan* p)
 {
     if (!p->adj) {
-        mm_status s = alloc(p, &p->adj, 16 * 3 * (size_t)p->N * elem_size(*p), "adjoint buffers");
+        mm_status s = alloc(p, &p->adj, 15 * 3 * (size_t)p->N * elem_size(*p), "adjoint buffers");
         if (s != MM_OK) return s;
     }
     if (!p->gms) {
@@ -838,28 +838,30 @@ using namespace mmx;
 namespace mmx {
 
 // Adjoint work-space layout (vectors of 3N): 0 y, 1 ynew, 2 ys, 3-6 k1..k4,
-// 7 z, 8 g, 9 lambda, 10 kappa, 11-14 nu1..nu4, 15 field scratch.
+// 7 z, 8 g, 9 lambda, 10 field scratch, 11-14 nu1..nu4.  What bounds a step of
+// forward and backward on a small grid is its launches, so the stage inputs are
+// formed in the x forward pass, the cotangents where they are read, and the
+// loss gradient is added with the adjoint update.
+//
+// One RK4 step y -> ynew.  With ys_store / hs_store the four stage inputs and
+// fields go there; the first input is y itself, which then is ys_store[0].
 template <typename T>
-static mm_status rk4_step_impl(Plan* p, T* y, T* ynew, const double hext[3], unsigned terms,
+static mm_status rk4_step_impl(Plan* p, const T* y, T* ynew, const double hext[3], unsigned terms,
                                double t, double dt, T* const* ys_store, T* const* hs_store)
 {
     T* k[4] = {adj_vec<T>(p, 3), adj_vec<T>(p, 4), adj_vec<T>(p, 5), adj_vec<T>(p, 6)};
-    T* ys = adj_vec<T>(p, 2);
     const double cs[4] = {0.0, 0.5, 0.5, 1.0};
-    const double half = 0.5, one = 1.0;
     for (int st = 0; st < 4; ++st) {
-        const T* in = y;
-        if (st > 0) {
-            T* prev = k[st - 1];
-            MM_HIP(rk_combine<T>(*p, ys, y, dt, st == 3 ? &one : &half, &prev, 1), "stage input");
-            in = ys;
+        T* h = hs_store ? hs_store[st] : nullptr;
+        if (st == 0) {
+            MM_HIP(eval_field<T>(*p, y, hext, terms, t, h, k[0], p->alpha, true, nullptr),
+                   "right-hand side");
+            continue;
         }
-        if (ys_store)
-            MM_HIP(hipMemcpyAsync(ys_store[st], in, 3 * (size_t)p->N * sizeof(T),
-                                  hipMemcpyDeviceToDevice, p->stream),
-                   "store stage");
-        MM_HIP(eval_field<T>(*p, in, hext, terms, t + cs[st] * dt, hs_store ? hs_store[st] : nullptr,
-                             k[st], p->alpha, true, nullptr),
+        const StageIn<T> sc = stage_in<T>(y, &k[st - 1], &cs[st], 1, dt, nullptr,
+                                          ys_store ? ys_store[st] : adj_vec<T>(p, 2));
+        MM_HIP(eval_field_stage<T>(*p, sc, hext, terms, t + cs[st] * dt, k[st], p->alpha, true,
+                                   nullptr, nullptr, h),
                "right-hand side");
     }
     const double b[4] = {1.0 / 6.0, 1.0 / 3.0, 1.0 / 3.0, 1.0 / 6.0};
@@ -872,11 +874,11 @@ static mm_status rk4_step_impl(Plan* p, T* y, T* ynew, const double hext[3], uns
 template <typename T>
 static mm_status count_region(Plan* p, const unsigned char* region, long* nreg)
 {
-    T* ind = adj_vec<T>(p, 15);
+    T* ind = adj_vec<T>(p, 10);
     MM_HIP(hipMemsetAsync(ind, 0, 3 * (size_t)p->N * sizeof(T), p->stream), "clear");
     MM_HIP(add_region<T>(*p, ind, region, 1.0), "region indicator");
-    MM_HIP(hipMemsetAsync(p->red_out + 7, 0, sizeof(double), p->stream), "clear");
-    MM_HIP(region_mz_accum<T>(*p, ind, region, p->red_out + 7, 1.0), "count region");
+    MM_HIP(region_mz<T>(*p, ind, region, false), "count region");
+    MM_HIP(region_mz_sum(*p, p->red_out + 7), "count region");
     mm_status s = fetch(p, 8);
     if (s != MM_OK) return s;
     *nreg = (long)std::llround(p->host_out[7]);
@@ -908,8 +910,9 @@ static mm_status rk4_forward_impl(Plan* p, void* m_user, const double hext[3], u
         s = rk4_step_impl<T>(p, y, ynew, hext, terms, t0 + n * dt, dt, nullptr, nullptr);
         if (s != MM_OK) return s;
         std::swap(y, ynew);
-        if (region && nreg > 0) MM_HIP(region_mz_accum<T>(*p, y, region, p->red_out + 6, 1.0), "loss");
+        if (region && nreg > 0) MM_HIP(region_mz<T>(*p, y, region, n > 0), "loss");
     }
+    if (region && nreg > 0 && nsteps > 0) MM_HIP(region_mz_sum(*p, p->red_out + 6), "loss");
     MM_HIP(hipMemcpyAsync(m_user, y, vb, hipMemcpyDeviceToDevice, p->stream), "copy m");
     s = fetch(p, 7);
     if (s != MM_OK) return s;
@@ -942,12 +945,9 @@ static mm_status rk4_adjoint_impl(Plan* p, const void* ckpt, const double hext[3
     if (s != MM_OK) return s;
     const double dL = nreg > 0 ? 1.0 / ((double)nsteps * nreg) : 0.0;
     const unsigned vterms = terms & ~(unsigned)(MM_ZEEMAN | MM_OERSTED);
-    T* y = adj_vec<T>(p, 0);
-    T* ynew = adj_vec<T>(p, 1);
     T* z = adj_vec<T>(p, 7);
     T* g = adj_vec<T>(p, 8);
     T* lam = adj_vec<T>(p, 9);
-    T* kap = adj_vec<T>(p, 10);
     T* nu[4] = {adj_vec<T>(p, 11), adj_vec<T>(p, 12), adj_vec<T>(p, 13), adj_vec<T>(p, 14)};
     MM_HIP(hipMemsetAsync(lam, 0, vb, p->stream), "clear lambda");
     MM_HIP(zero_doubles(*p, p->gms, p->N), "clear gradient");
@@ -955,44 +955,40 @@ static mm_status rk4_adjoint_impl(Plan* p, const void* ckpt, const double hext[3
     const long nseg = (nsteps + every - 1) / every;
     auto Ys = [&](long i, int st) { return (T*)p->seg + ((size_t)i * 8 + st) * 3 * p->N; };
     auto Hs = [&](long i, int st) { return (T*)p->seg + ((size_t)i * 8 + 4 + st) * 3 * p->N; };
+    bool first = true;  // no block sums of the loss yet
     for (long sg = nseg - 1; sg >= 0; --sg) {
         const long n0 = sg * every, n1 = std::min(nsteps, n0 + every);
-        MM_HIP(hipMemcpyAsync(y, (const T*)ckpt + (size_t)sg * 3 * p->N, vb,
+        MM_HIP(hipMemcpyAsync(Ys(0, 0), (const T*)ckpt + (size_t)sg * 3 * p->N, vb,
                               hipMemcpyDeviceToDevice, p->stream),
                "restore checkpoint");
         for (long n = n0; n < n1; ++n) {
-            T* ysv[4] = {Ys(n - n0, 0), Ys(n - n0, 1), Ys(n - n0, 2), Ys(n - n0, 3)};
-            T* hsv[4] = {Hs(n - n0, 0), Hs(n - n0, 1), Hs(n - n0, 2), Hs(n - n0, 3)};
-            s = rk4_step_impl<T>(p, y, ynew, hext, terms, t0 + n * dt, dt, ysv, hsv);
+            const long i = n - n0;
+            T* ysv[4] = {Ys(i, 0), Ys(i, 1), Ys(i, 2), Ys(i, 3)};
+            T* hsv[4] = {Hs(i, 0), Hs(i, 1), Hs(i, 2), Hs(i, 3)};
+            // the new state is the next step's first stage input
+            T* ynew = n + 1 < n1 ? Ys(i + 1, 0) : adj_vec<T>(p, 1);
+            s = rk4_step_impl<T>(p, ysv[0], ynew, hext, terms, t0 + n * dt, dt, ysv, hsv);
             if (s != MM_OK) return s;
-            std::swap(y, ynew);
-            MM_HIP(region_mz_accum<T>(*p, y, region, p->red_out + 6, 1.0), "loss");
+            MM_HIP(region_mz<T>(*p, ynew, region, !first), "loss");
+            first = false;
         }
+        if (sg == nseg - 1) MM_HIP(add_region<T>(*p, lam, region, dL), "loss gradient");
         for (long n = n1 - 1; n >= n0; --n) {
             const long i = n - n0;
-            MM_HIP(add_region<T>(*p, lam, region, dL), "loss gradient");
             // kappa_4 = dt/6 lam;  kappa_3 = dt/3 lam + dt nu_4;
             // kappa_2 = dt/3 lam + dt/2 nu_3;  kappa_1 = dt/6 lam + dt/2 nu_2
             const double cl[4] = {dt / 6.0, dt / 3.0, dt / 3.0, dt / 6.0};
             const double cn[4] = {0.0, 0.5 * dt, 0.5 * dt, dt};
-            for (int st = 3; st >= 0; --st) {
-                if (st == 3) {
-                    T* v1[1] = {lam};
-                    MM_HIP(lincomb<T>(*p, kap, &cl[3], v1, 1), "cotangent");
-                } else {
-                    T* v2[2] = {lam, nu[st + 1]};
-                    const double c2[2] = {cl[st], cn[st + 1]};
-                    MM_HIP(lincomb<T>(*p, kap, c2, v2, 2), "cotangent");
-                }
-                MM_HIP(field_vjp<T>(*p, Ys(i, st), kap, Hs(i, st), vterms, p->alpha, g, z, nu[st],
-                                    p->gms),
+            for (int st = 3; st >= 0; --st)
+                MM_HIP(field_vjp<T>(*p, Ys(i, st), lam, Hs(i, st), vterms, p->alpha, g, z, nu[st],
+                                    p->gms, cl[st], st < 3 ? nu[st + 1] : nullptr,
+                                    st < 3 ? cn[st + 1] : 0.0),
                        "vector-Jacobian product");
-            }
-            T* v5[5] = {lam, nu[0], nu[1], nu[2], nu[3]};
-            const double c5[5] = {1.0, 1.0, 1.0, 1.0, 1.0};
-            MM_HIP(lincomb<T>(*p, lam, c5, v5, 5), "adjoint update");
+            // with the loss gradient of the step before
+            MM_HIP(adj_update<T>(*p, lam, nu, n > 0 ? region : nullptr, dL), "adjoint update");
         }
     }
+    if (!first) MM_HIP(region_mz_sum(*p, p->red_out + 6), "loss");
     if (grad_m0)
         MM_HIP(hipMemcpyAsync(grad_m0, lam, vb, hipMemcpyDeviceToDevice, p->stream), "grad m0");
     if (grad_ms) MM_HIP(from_double<T>(*p, p->gms, (T*)grad_ms, p->N), "grad Ms");
@@ -1035,7 +1031,7 @@ static mm_status heff_vjp_impl(Plan* p, const T* m, const T* w, const double hex
     if (s != MM_OK) return s;
     T* h = nullptr;
     if (llg) {
-        h = adj_vec<T>(p, 15);
+        h = adj_vec<T>(p, 10);
         MM_HIP(eval_field<T>(*p, m, hext, terms, t, h, nullptr, p->alpha, true, nullptr), "field");
     }
     MM_HIP(zero_doubles(*p, p->gms, p->N), "clear gradient");

@@ -208,7 +208,7 @@ struct ErrIn {
 template <typename T>
 hipError_t eval_field_stage(Plan &p, const StageIn<T> &sc, const double hext[3], unsigned terms,
                             double t, T *dm_out, double alpha_eff, bool precess, double *torque,
-                            const ErrIn<T> *err = nullptr);
+                            const ErrIn<T> *err = nullptr, T *h_out = nullptr);
 // Whether eval_field_stage can accumulate the error norm (ErrIn, sc.ep set)
 // for this plan and terms: the demag chain runs, the plain stencil, one
 // request, the wave-local local pass, the partials buffer in place.
@@ -302,16 +302,19 @@ hipError_t count_signs(Plan &p, const T *v, double *out_dev);
 // (w masked to magnetic cells).  With h (the field at m): nu = J^T w of the
 // LLG right-hand side with damping alpha.  gms (double, may be null)
 // accumulates d(w.h)/dMs resp. d(w.f)/dMs.  g_tmp and z_tmp are 3N scratch.
+// The cotangent is cl w + cn nu_in (nu_in may be null).
 template <typename T>
 hipError_t field_vjp(Plan &p, const T *m, const T *w, const T *h, unsigned terms, double alpha,
-                     T *g_tmp, T *z_tmp, T *nu, double *gms);
-// out = sum_{j < nk} c[j] v[j]  (nk <= 6)
+                     T *g_tmp, T *z_tmp, T *nu, double *gms, double cl = 1.0,
+                     const T *nu_in = nullptr, double cn = 0.0);
+// lam += nu[0] + nu[1] + nu[2] + nu[3], lam_z += val on the region (may be null)
 template <typename T>
-hipError_t lincomb(Plan &p, T *out, const double *c, T *const *v, int nk);
-// *out_dev += scale * sum over region of m_z
+hipError_t adj_update(Plan &p, T *lam, T *const *nu, const unsigned char *region, double val);
+// block sums of m_z over the region into p.red (add: onto the ones there), and
+// their total into *out_dev
 template <typename T>
-hipError_t region_mz_accum(Plan &p, const T *m, const unsigned char *region, double *out_dev,
-                           double scale);
+hipError_t region_mz(Plan &p, const T *m, const unsigned char *region, bool add);
+hipError_t region_mz_sum(Plan &p, double *out_dev);
 // lam_z += val on the region
 template <typename T>
 hipError_t add_region(Plan &p, T *lam, const unsigned char *region, double val);

@@ -549,16 +549,28 @@ __global__ __launch_bounds__(kBlock) void k_count_signs(const T* __restrict__ v,
 // cotangent w:  d(w.f)/dm|_h = -g' [h x w + alpha (w (m.h) + h (w.m) - 2 m (w.h))]
 //               z = d(w.f)/dh = -g' [w x m + alpha (m (w.m) - w |m|^2)].
 // ---------------------------------------------------------------------------
-// g (may be null: then z is w masked to magnetic cells) and z per cell.
+// g (may be null: then z is w masked to magnetic cells) and z per cell.  The
+// cotangent is w, or with nu (or cl != 1) cl w + cn nu, formed as it is read.
 template <typename T, bool PERCELL>
 __global__ void k_vjp_pre(const T* __restrict__ m, const T* __restrict__ h,
                           const T* __restrict__ w, const T* __restrict__ Ms_cell, T Ms, long N,
-                          T gp, T alpha, T* __restrict__ g_out, T* __restrict__ z_out)
+                          T gp, T alpha, T* __restrict__ g_out, T* __restrict__ z_out, T cl,
+                          const T* __restrict__ nu, T cn)
 {
     for (long q = (long)blockIdx.x * blockDim.x + threadIdx.x; q < N;
          q += (long)gridDim.x * blockDim.x) {
         const T ms = PERCELL ? Ms_cell[q] : Ms;
-        const T wx = w[q], wy = w[N + q], wz = w[2 * N + q];
+        T wx = w[q], wy = w[N + q], wz = w[2 * N + q];
+        if (cl != (T)1) {
+            wx *= cl;
+            wy *= cl;
+            wz *= cl;
+        }
+        if (nu) {
+            wx += cn * nu[q];
+            wy += cn * nu[N + q];
+            wz += cn * nu[2 * N + q];
+        }
         if (ms == (T)0) {
             z_out[q] = z_out[N + q] = z_out[2 * N + q] = (T)0;
             if (g_out) g_out[q] = g_out[N + q] = g_out[2 * N + q] = (T)0;
@@ -731,40 +743,34 @@ __global__ __launch_bounds__((XFORM ? XC2RW<T, M, TR>::kNT : 256)) void k_adj_lo
     }
 }
 
-// out = sum_{j < NK} c_j v_j
-template <typename T, int NK>
-__global__ void k_lincomb(T* __restrict__ out, Coef7 cf, Ptr7<T> v, long n3)
+// lam += nu_0 + nu_1 + nu_2 + nu_3, and lam_z += val on the region (the loss
+// gradient of the step before; region may be null)
+template <typename T>
+__global__ void k_adj_update(T* __restrict__ lam, Ptr7<T> nu, const unsigned char* __restrict__ region,
+                             T val, long N)
 {
-    for (long q = (long)blockIdx.x * blockDim.x + threadIdx.x; q < n3;
+    for (long q = (long)blockIdx.x * blockDim.x + threadIdx.x; q < 3 * N;
          q += (long)gridDim.x * blockDim.x) {
-        T acc = (T)0;
+        T acc = lam[q];
 #pragma unroll
-        for (int j = 0; j < NK; ++j) acc += (T)cf.c[j] * v.p[j][q];
-        out[q] = acc;
+        for (int j = 0; j < 4; ++j) acc += nu.p[j][q];
+        if (region && q >= 2 * N && region[q - 2 * N]) acc += val;
+        lam[q] = acc;
     }
 }
 
-// partial sums of m_z over a region mask
+// partial sums of m_z over a region mask (added to the block's last ones)
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_region_mz(const T* __restrict__ m,
                                                       const unsigned char* __restrict__ region,
-                                                      long N, double* partials)
+                                                      long N, double* partials, bool add)
 {
     double acc = 0.0;
     for (long q = (long)blockIdx.x * blockDim.x + threadIdx.x; q < N;
          q += (long)gridDim.x * blockDim.x)
         if (region[q]) acc += (double)m[2 * N + q];
     acc = block_sum(acc);
-    if (threadIdx.x == 0) partials[blockIdx.x] = acc;
-}
-
-// *out += scale * sum(partials[0..n))
-__global__ void k_final_accum(const double* __restrict__ partials, int n, double* out, double scale)
-{
-    double v = 0.0;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) v += partials[i];
-    v = block_sum(v);
-    if (threadIdx.x == 0) *out += scale * v;
+    if (threadIdx.x == 0) partials[blockIdx.x] = add ? partials[blockIdx.x] + acc : acc;
 }
 
 // lam_z += val on the region
@@ -1876,12 +1882,12 @@ hipError_t eval_field(Plan& p, const T* m, const double hext[3], unsigned terms,
 template <typename T>
 hipError_t eval_field_stage(Plan& p, const StageIn<T>& sc, const double hext[3], unsigned terms,
                             double t, T* dm_out, double alpha_eff, bool precess, double* torque,
-                            const ErrIn<T>* err)
+                            const ErrIn<T>* err, T* h_out)
 {
     if (sc.nk < 1 || sc.nk > 7 || !sc.y || !sc.ys) return hipErrorInvalidValue;
     if (err || sc.ep) {
         if (!(err && sc.ep) || !err_fusable(p, terms)) return hipErrorInvalidValue;
-        return eval_field_core<T>(p, sc.ys, hext, terms, t, nullptr, dm_out, alpha_eff, precess,
+        return eval_field_core<T>(p, sc.ys, hext, terms, t, h_out, dm_out, alpha_eff, precess,
                                   torque, &sc, err);
     }
     // a batch forms its stage inputs in the combination kernel (one step
@@ -1889,10 +1895,10 @@ hipError_t eval_field_stage(Plan& p, const StageIn<T>& sc, const double hext[3],
     if (!(terms & MM_DEMAG) || p.P[0] / 2 < 2 || p.Pb) {
         MMX_TRY(rk_combine<T>(p, sc.ys, sc.y, 1.0, sc.c, const_cast<T* const*>(sc.k), sc.nk,
                               sc.h));
-        return eval_field_core<T>(p, sc.ys, hext, terms, t, nullptr, dm_out, alpha_eff, precess,
+        return eval_field_core<T>(p, sc.ys, hext, terms, t, h_out, dm_out, alpha_eff, precess,
                                   torque, nullptr);
     }
-    return eval_field_core<T>(p, sc.ys, hext, terms, t, nullptr, dm_out, alpha_eff, precess,
+    return eval_field_core<T>(p, sc.ys, hext, terms, t, h_out, dm_out, alpha_eff, precess,
                               torque, &sc);
 }
 
@@ -2106,17 +2112,18 @@ hipError_t count_signs(Plan& p, const T* v, double* out_dev)
 // ---------------------------------------------------------------------------
 template <typename T>
 hipError_t field_vjp(Plan& p, const T* m, const T* w, const T* h, unsigned terms, double alpha,
-                     T* g_tmp, T* z_tmp, T* nu, double* gms)
+                     T* g_tmp, T* z_tmp, T* nu, double* gms, double cl, const T* nu_in, double cn)
 {
     const int blocks = (int)std::min<long>(blocks_for(p.N, 256), 4096);
     const double gp = kGamma / (1.0 + alpha * alpha);
     if (p.percell)
         k_vjp_pre<T, true><<<blocks, 256, 0, p.stream>>>(m, h, w, (const T*)p.Ms_cell, (T)p.Ms, p.N,
                                                        (T)gp, (T)alpha, h ? g_tmp : nullptr,
-                                                       z_tmp);
+                                                       z_tmp, (T)cl, nu_in, (T)cn);
     else
         k_vjp_pre<T, false><<<blocks, 256, 0, p.stream>>>(m, h, w, nullptr, (T)p.Ms, p.N, (T)gp,
-                                                        (T)alpha, h ? g_tmp : nullptr, z_tmp);
+                                                        (T)alpha, h ? g_tmp : nullptr, z_tmp,
+                                                        (T)cl, nu_in, (T)cn);
     MMX_TRY(hipGetLastError());
     const bool demag = (terms & MM_DEMAG) != 0;
     if (demag) MMX_TRY(demag_to_S1<T>(p, z_tmp, false));
@@ -2146,37 +2153,27 @@ hipError_t field_vjp(Plan& p, const T* m, const T* w, const T* h, unsigned terms
 }
 
 template <typename T>
-hipError_t lincomb(Plan& p, T* out, const double* c, T* const* v, int nk)
+hipError_t adj_update(Plan& p, T* lam, T* const* nu, const unsigned char* region, double val)
 {
-    Coef7 cf{};
     Ptr7<T> ps{};
-    for (int j = 0; j < nk; ++j) {
-        cf.c[j] = c[j];
-        ps.p[j] = v[j];
-    }
-    const long n3 = 3 * p.N;
-    const int blocks = (int)std::min<long>(blocks_for(n3, 256), 8192);
+    for (int j = 0; j < 4; ++j) ps.p[j] = nu[j];
+    const int blocks = (int)std::min<long>(blocks_for(3 * p.N, 256), 8192);
     return timed(p, MM_PASS_RK, [&] {
-        switch (nk) {
-        case 1: k_lincomb<T, 1><<<blocks, 256, 0, p.stream>>>(out, cf, ps, n3); break;
-        case 2: k_lincomb<T, 2><<<blocks, 256, 0, p.stream>>>(out, cf, ps, n3); break;
-        case 3: k_lincomb<T, 3><<<blocks, 256, 0, p.stream>>>(out, cf, ps, n3); break;
-        case 4: k_lincomb<T, 4><<<blocks, 256, 0, p.stream>>>(out, cf, ps, n3); break;
-        case 5: k_lincomb<T, 5><<<blocks, 256, 0, p.stream>>>(out, cf, ps, n3); break;
-        case 6: k_lincomb<T, 6><<<blocks, 256, 0, p.stream>>>(out, cf, ps, n3); break;
-        default: return hipErrorInvalidValue;
-        }
+        k_adj_update<T><<<blocks, 256, 0, p.stream>>>(lam, ps, region, (T)val, p.N);
         return hipGetLastError();
     });
 }
 
 template <typename T>
-hipError_t region_mz_accum(Plan& p, const T* m, const unsigned char* region, double* out_dev,
-                           double scale)
+hipError_t region_mz(Plan& p, const T* m, const unsigned char* region, bool add)
 {
-    k_region_mz<T><<<kRedBlocks, kBlock, 0, p.stream>>>(m, region, p.N, p.red);
-    MMX_TRY(hipGetLastError());
-    k_final_accum<<<1, kBlock, 0, p.stream>>>(p.red, kRedBlocks, out_dev, scale);
+    k_region_mz<T><<<kRedBlocks, kBlock, 0, p.stream>>>(m, region, p.N, p.red, add);
+    return hipGetLastError();
+}
+
+hipError_t region_mz_sum(Plan& p, double* out_dev)
+{
+    k_final_sum<<<1, kBlock, 0, p.stream>>>(p.red, kRedBlocks, out_dev, 0, 1.0, 0);
     return hipGetLastError();
 }
 
@@ -2446,7 +2443,7 @@ hipError_t from_double(Plan& p, const double* in, T* out, long n)
                                       double, bool, double*, const T*);                          \
     template hipError_t eval_field_stage<T>(Plan&, const StageIn<T>&, const double*, unsigned,   \
                                             double, T*, double, bool, double*,                   \
-                                            const ErrIn<T>*);                                    \
+                                            const ErrIn<T>*, T*);                                \
     template hipError_t rk_combine<T>(Plan&, T*, const T*, double, const double*, T* const*,     \
                                       int, const double*);                                       \
     template hipError_t rk_error_norm<T>(Plan&, const T*, const T*, double, const double*,       \
@@ -2463,10 +2460,9 @@ hipError_t from_double(Plan& p, const double* in, T* out, long n)
     template hipError_t oersted_field<T>(Plan&, const T*, T*);                                   \
     template hipError_t debug_spectrum<T>(Plan&, int, double*);                                  \
     template hipError_t field_vjp<T>(Plan&, const T*, const T*, const T*, unsigned, double, T*,  \
-                                     T*, T*, double*);                                           \
-    template hipError_t lincomb<T>(Plan&, T*, const double*, T* const*, int);                    \
-    template hipError_t region_mz_accum<T>(Plan&, const T*, const unsigned char*, double*,       \
-                                           double);                                              \
+                                     T*, T*, double*, double, const T*, double);                 \
+    template hipError_t adj_update<T>(Plan&, T*, T* const*, const unsigned char*, double);       \
+    template hipError_t region_mz<T>(Plan&, const T*, const unsigned char*, bool);               \
     template hipError_t add_region<T>(Plan&, T*, const unsigned char*, double);                  \
     template hipError_t from_double<T>(Plan&, const double*, T*, long);
 

@@ -176,6 +176,44 @@ def test_adjoint_independent_of_checkpoint_interval(torch_cuda, mm, orc):
         assert np.array_equal(to_np(gm0), to_np(res[0][2]))
 
 
+@pytest.mark.parametrize("grid", [(1, 7, 5), (9, 6, 1), (40, 3, 2)])
+@pytest.mark.parametrize("terms", ["ALL", "EXCH|ANIS|ZEEMAN"])
+def test_rk4_adjoint_is_the_loss_gradient(torch_cuda, mm, orc, terms, grid):
+    """Stage inputs formed in the x forward pass or (no demagnetising field, one
+    cell along x) by the combination kernel, cotangents formed in the
+    vector-Jacobian product: the directional derivative of the loss by Ms and
+    m0 in double.  Central differences of step e carry an error of e^2 (third
+    derivatives of order one in relative steps) + 1e-16/e: 1e-5 at e = 1e-4."""
+    bits = mm.MM_ALL if terms == "ALL" else mm.MM_EXCH | mm.MM_ANIS | mm.MM_ZEEMAN
+    g = W.rng(sum(grid))
+    nx, ny, nz = grid
+    Ms = g.uniform(4e5, 1.2e6, (nz, ny, nx))
+    m0 = W.random_unit_sphere(grid, 5)
+    region = (g.uniform(size=Ms.shape) < 0.5).astype(np.uint8)
+    region[0, 0, 0] = 1
+    H, dt, nsteps, every = np.array([3e3, 0.0, 1.2e4]), 1e-13, 8, 3
+
+    def run(ms, m, grad=False):
+        plan, _ = _pair(mm, orc, grid, (5e-9, 5e-9, 4e-9), ms, "fp64")
+        y = plan._t(m)
+        loss, ck = plan.rk4(y, dt, nsteps, region, H, bits, 0.0, ckpt_every=every)
+        if not grad:
+            return loss
+        la, gms, gm0 = plan.rk4_adjoint(ck, dt, nsteps, region, H, bits, 0.0, every)
+        assert abs(la - loss) <= 1e-12 * abs(loss)
+        return to_np(gms), to_np(gm0)
+
+    gms, gm0 = run(Ms, m0, True)
+    e = 1e-4
+    u = g.standard_normal(Ms.shape) * Ms
+    v = g.standard_normal(m0.shape)
+    for got, fd in (((gms * u).sum(), run(Ms + e * u, m0) - run(Ms - e * u, m0)),
+                    ((gm0 * v).sum(), run(Ms, m0 + e * v) - run(Ms, m0 - e * v))):
+        fd /= 2 * e
+        print("  %.9e %.9e" % (got, fd))
+        assert abs(got - fd) <= 1e-5 * max(abs(got), abs(fd)), (got, fd)
+
+
 def test_rk4_adjoint_invalid_arguments(torch_cuda, mm, orc):
     banner("rk4 adjoint invalid arguments")
     plan, _, m0, H, region, _ = _rk4_case(mm, orc, "fp64")
