@@ -43,9 +43,10 @@ namespace mmx {
 #ifndef MMX_RX1_F64
 #define MMX_RX1_F64 8
 #endif
-// threads per block targeted by the strided and last-axis passes
+// threads per block targeted by the strided and last-axis passes (the strided
+// ones hold at least a 128-byte line of columns)
 #ifndef MMX_SBLOCK
-#define MMX_SBLOCK 512
+#define MMX_SBLOCK 128
 #endif
 #ifndef MMX_MBLOCK
 #define MMX_MBLOCK 256
@@ -78,11 +79,6 @@ namespace mmx {
 #endif
 #ifndef MMX_RMW_F64
 #define MMX_RMW_F64 8
-#endif
-#ifdef MMX_STRIDED_WPE
-#define MMX_STRIDED_ATTR __attribute__((amdgpu_waves_per_eu(MMX_STRIDED_WPE)))
-#else
-#define MMX_STRIDED_ATTR
 #endif
 // F1 in FP32: 96 VGPRs give 5 waves per SIMD (measured -3 % at 512x512x64)
 #ifndef MMX_XR2C_WPE_F32
@@ -459,9 +455,25 @@ __global__ __launch_bounds__((XR2C<T, M, TR>::kRows * XR2C<T, M, TR>::kT)) MMX_X
 // ---------------------------------------------------------------------------
 template <typename T, int L>
 struct Strided {
-    using S = FFTShape<L, Regs<T>::s>;
+    // FP32 transforms of at most 256 points with 16 values per thread instead of
+    // 32: y forward and inverse at 128 x 128 x 64 20.5 -> 17.8 and 20.6 -> 17.3
+    // us; at 512 and 1024 points (two exchanges instead of one) 59 -> 72 and
+    // 258 -> 381 us, so they keep 32
+    static constexpr int kRegs = sizeof(T) == 4 && L <= 256 ? 16 : Regs<T>::s;
+    using S = FFTShape<L, kRegs>;
     static constexpr int kE = S::kE, kT = S::kT;
-    static constexpr int kB = cmin(64, cmax(1, MMX_SBLOCK / kT));
+    // one 128-byte line of columns, more only up to MMX_SBLOCK threads: a block
+    // loads, transforms and stores in turn, so a compute unit streams only while
+    // it holds several.  Against 512 threads for every length, forward and
+    // inverse, FP32: 128 x 128 x 64 28.0 and 29.8 -> 20.5 and 20.6 us,
+    // 512 x 256 x 32 71 and 81 -> 59 and 65; FP64: 127 and 147 -> 115 and 126.
+    // Half lines: 512 x 512 x 64 258 and 287 -> 314 and 319
+    static constexpr int kB = cmin(64, cmax(128 / (int)sizeof(cx<T>), MMX_SBLOCK / kT));
+    // waves per SIMD asked of the compiler: forward FP64 at 1024 points needs
+    // 128 registers for two blocks per compute unit (512 x 512 x 64: 538 -> 471
+    // us); the inverse spills for it (471 -> 486)
+    template <int DIR, bool O32>
+    static constexpr int kWaves = sizeof(T) == 8 && L == 1024 && DIR < 0 && O32 ? 4 : 1;
 };
 
 // HALF (forward): n_in <= L/2, the upper half of the inputs is zero padding.
@@ -469,7 +481,8 @@ struct Strided {
 // O32: every element offset of `in` and `out` times its size is below 4 GiB
 // (32-bit index arithmetic, scalar base + vector byte offset accesses).
 template <typename T, int L, int DIR, bool HALF, bool O32>
-__global__ __launch_bounds__((Strided<T, L>::kB * Strided<T, L>::kT)) MMX_STRIDED_ATTR void k_strided(
+__global__ __launch_bounds__((Strided<T, L>::kB * Strided<T, L>::kT),
+                             (Strided<T, L>::template kWaves<DIR, O32>)) void k_strided(
     const cx<T>* in, cx<T>* out, int n_in, int n_out, long es_in, long es_out, int ncols,
     int ntile, int G2, long nblocks, long g1_in, long g1_out, long g2_in, long g2_out,
     const cx<T>* __restrict__ tw, int Lmax)
@@ -499,7 +512,7 @@ __global__ __launch_bounds__((Strided<T, L>::kB * Strided<T, L>::kT)) MMX_STRIDE
                                                           : cx<T>{0, 0};
     }
     cx<T>* lb_ = SPL ? reinterpret_cast<cx<T>*>(reinterpret_cast<T*>(lds) + b) : lds + b;
-    WgFFT<T, L, Regs<T>::s, DIR, HIN, SPL>::run(v, t, lb_, kB, tw, Lmax / L);
+    WgFFT<T, L, G::kRegs, DIR, HIN, SPL>::run(v, t, lb_, kB, tw, Lmax / L);
     if (!cv) return;
     constexpr int Rl = G::S::kLast;
 #pragma unroll
