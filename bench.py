@@ -31,9 +31,10 @@ METRIC = "Heff evals×cells/s at 16.7M cells FP32 vs FP64; p50/p99 batched solve
 HBM_PEAK_GBS = 8000.0
 
 
-def pass_bytes(grid, prec):
+def pass_bytes(grid, prec, plane=False):
     """Algorithmic HBM bytes per launch of each pass (the traffic model: every
-    array a pass must read or write, once)."""
+    array a pass must read or write, once).  plane: the y and z transforms and
+    the product are one kernel ("mid"), there are no y passes."""
     nx, ny, nz = grid
     P = [1 if n == 1 else 1 << (2 * n - 2).bit_length() for n in grid]
     Px, Py, Pz = P
@@ -44,6 +45,8 @@ def pass_bytes(grid, prec):
     S2 = 3 * hx * Py * nz * 2 * w
     K = 6 * hx * (Py // 2 + 1) * (Pz // 2 + 1) * w
     m = 3 * N * w
+    if plane:
+        return {"x_fwd": m + S1, "mid": 2 * S1 + K, "x_inv_local": S1 + m + m}
     return {"x_fwd": m + S1, "y_fwd": S1 + S2, "mid": 2 * S2 + K, "y_inv": S2 + S1,
             "x_inv_local": S1 + m + m}
 
@@ -118,7 +121,7 @@ def heff_only(mm, plan, m, cfg, iters, profile=False):
 DP45_STAGE_K = (1, 2, 3, 4, 5, 5)
 
 
-def step_bytes(grid, prec):
+def step_bytes(grid, prec, plane=False):
     """Algorithmic bytes per launch of the kernels of a Dormand-Prince step,
     averaged over its six stages: the x forward pass with the stage input
     formed in its load (y, the k_j of non-zero a_sj, the stage input written;
@@ -126,7 +129,7 @@ def step_bytes(grid, prec):
     (the last stage also reads the partial error and y for the error norm),
     and the error norm as a kernel of its own where it runs (y, y1 and the
     six k_j of non-zero b_j - b*_j)."""
-    pb = pass_bytes(grid, prec)
+    pb = pass_bytes(grid, prec, plane)
     w = 4 if prec == "fp32" else 8
     m = 3 * grid[0] * grid[1] * grid[2] * w
     ns = len(DP45_STAGE_K)
@@ -437,13 +440,13 @@ def throughput_c2(mm, W, iters):
             if seed == 0:
                 pr = plan.profile_read()
                 plan.profile(False)
-                pb = pass_bytes(c["n"], prec)
+                pb = pass_bytes(c["n"], prec, plane=not pr["y_fwd"][1])
                 passes = {k: {"avg_us": 1e3 * v[0] / v[1], "GBs": pb[k] / (v[0] / 1e3 / v[1]) / 1e9}
                           for k, v in pr.items() if v[1] and k in pb}
             del plan, m, h
         N = 256 * 256 * 16
         wall = float(np.median(walls))
-        byt = sum(pass_bytes((256, 256, 16), prec).values())
+        byt = sum(pb.values())
         out[prec] = {"cell_evals_per_s": N / wall, "ms": 1e3 * wall, "model_bytes": byt,
                      "GBs": byt / wall / 1e9, "roofline_frac_cache_assisted": byt / wall / 1e9 /
                      HBM_PEAK_GBS, "passes": passes, "runs": [1e3 * w for w in walls]}
@@ -651,7 +654,8 @@ def main():
     evals = r32["stats"]["rhs_evals"]
     value = evals * N / r32["wall"]
     prof = r32["prof"]
-    pb = pass_bytes(grid, "fp32")
+    plane = not prof["y_fwd"][1]
+    pb = pass_bytes(grid, "fp32", plane)
     mid_ms, mid_n = prof["mid"]
     mid_avg_s = mid_ms / 1e3 / mid_n
     achieved = pb["mid"] / mid_avg_s / 1e9
@@ -666,7 +670,7 @@ def main():
             gbs = pb[k] / (ms / 1e3 / n) / 1e9
             passes[k] = {"avg_us": 1e3 * ms / n, "launches": n, "model_bytes": pb[k],
                          "GBs": gbs, "frac": gbs / HBM_PEAK_GBS}
-    sb = step_bytes(grid, "fp32")
+    sb = step_bytes(grid, "fp32", plane)
     step_k = {}
     for k, name in (("x_fwd", "x_fwd_stage"), ("y_fwd", "y_fwd"), ("mid", "mid"),
                     ("y_inv", "y_inv"), ("x_inv_local", "x_inv_local"), ("rk", "rk")):

@@ -19,9 +19,10 @@
 //
 // With a single layer (Pz = 1) F2/F3/I2 collapse into one kernel (y forward,
 // product, y inverse), and on grids whose y-z plane fits a compute unit too
-// (plane.h), on a spectrum laid out for it.  The 1/(Px Py Pz) of the inverse transform is folded
-// into the resident spectral kernel.  No MFMA: FFTs and stencils are not dense
-// contractions; everything here is VALU + LDS, bounded by HBM traffic.
+// (plane.h), on a spectrum laid out for it.  The 1/(Px Py Pz) of the inverse
+// transform is folded into the resident spectral kernel.  No MFMA: FFTs and
+// stencils are not dense contractions; everything here is VALU + LDS, bounded
+// by HBM traffic and VALU issue on large grids and by latency on small ones.
 #include <cstring>
 
 #include "passes.h"
