@@ -113,7 +113,7 @@ struct Plan {
     double *red_out = nullptr;  // reduction results (8 doubles)
     double *host_out = nullptr; // pinned host mirror of red_out
     // differentiation work space (allocated on first use)
-    void *adj = nullptr;        // 16 vectors of 3N
+    void *adj = nullptr;        // 15 vectors of 3N
     void *seg = nullptr;        // stage states and fields of one checkpoint segment
     size_t seg_bytes = 0;
     double *gms = nullptr;      // N doubles: Ms-gradient accumulator

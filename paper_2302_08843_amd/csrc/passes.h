@@ -1835,16 +1835,22 @@ static hipError_t launch_mid_L(const Plan& p, cx<T>* S, int n_valid, long es, lo
     const int groups = (AXIS == 2 && G > 1) ? G / 2 + 1 : G;
     const bool o32 = (size_t)p.S2n * 2 * sizeof(T) < (1ull << 32);
     const bool half = 2 * n_valid <= L && L > 1;
+    // whole lines (Hc) only where they cost no sixteenth more columns: on narrow
+    // grids the padding is up to as much again as the columns themselves
+    // (z pass with Hc and with Hx: 7 x 347 x 65 FP64 63.8 and 47.1 us,
+    // 13 x 400 x 90 FP32 59.0 and 45.9, 128 x 128 x 64 FP32 40.4 and 38.2).
+    // The columns from Hx on hold transforms that nothing reads.
+    const int ncols = p.Hc - p.Hx > p.Hx / 16 ? p.Hx : p.Hc;
     if constexpr (MMX_MIDW && MidW<T, L>::kOK) {
         using Gw = MidW<T, L>;
-        const int ntile = (p.Hc + Gw::kCB - 1) / Gw::kCB;
+        const int ntile = (ncols + Gw::kCB - 1) / Gw::kCB;
         const int ntb = ntile;
         const long nb = AXIS == 2 ? (long)ntb * groups : (ntile + Gw::kW - 1) / Gw::kW;
         // a batch: the requests' spectra follow each other, 3 components apart
         const int nbatch = p.batch > 1 ? p.batch : 1;
 #define MMX_KMIDW(H, O)                                                                           \
     k_mid_w<T, L, AXIS, H, O, PROD><<<xcd_grid(nb * nbatch), 64 * Gw::kW, 0, p.stream>>>(         \
-        S, (const T*)p.Khat, n_valid, es, cs, gstride, p.Hc, ntb, nb, p.P[1], p.P[2], p.Hxp,     \
+        S, (const T*)p.Khat, n_valid, es, cs, gstride, ncols, ntb, nb, p.P[1], p.P[2], p.Hxp,     \
         (const cx<T>*)p.tw, p.Lmax, nbatch, 3 * cs)
         if (half && o32)
             MMX_KMIDW(true, true);
@@ -1859,7 +1865,7 @@ static hipError_t launch_mid_L(const Plan& p, cx<T>* S, int n_valid, long es, lo
     } else {
     if (p.batch > 1) return hipErrorInvalidValue;  // batches need the wave-local kernel
     using Gm = Mid<T, L>;
-    const int ntile = (p.Hc + Gm::kB - 1) / Gm::kB;
+    const int ntile = (ncols + Gm::kB - 1) / Gm::kB;
     const long nblocks = (long)ntile * groups;
     // the Oersted product (PROD 1) uses the paired-in-block order only
     const bool adj = PROD == 0 && (sizeof(T) == 4 ? MMX_MID_ADJ_F32 : MMX_MID_ADJ_F64) &&
@@ -1867,7 +1873,7 @@ static hipError_t launch_mid_L(const Plan& p, cx<T>* S, int n_valid, long es, lo
     const long nb = adj ? 2 * nblocks : nblocks;
 #define MMX_KMID(H, O, AD)                                                                        \
     k_mid<T, L, AXIS, H, O, AD, PROD><<<xcd_grid(nb), Gm::kB * Gm::kT, 0, p.stream>>>(            \
-        S, (const T*)p.Khat, n_valid, es, cs, gstride, p.Hc, ntile, nb, p.P[1], p.P[2], p.Hxp,   \
+        S, (const T*)p.Khat, n_valid, es, cs, gstride, ncols, ntile, nb, p.P[1], p.P[2], p.Hxp,   \
         (const cx<T>*)p.tw, p.Lmax)
 #define MMX_KMID2(H, O)                  \
     if constexpr (PROD == 0) {           \

@@ -59,3 +59,22 @@ def test_field_and_transpose(mm, orc, grid, prec):
     ref, ref_ms = o.heff_vjp(m, w, terms=orc.DEMAG)
     assert rel_l2(to_np(gm), ref) <= BAR[prec]
     assert rel_l2(to_np(gms), ref_ms) <= BAR[prec]
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("grid", [(7, 12, 65), (3, 9, 70), (20, 33, 130), (33, 12, 34),
+                                  (120, 6, 65), (260, 5, 66)])
+def test_narrow_rows_through_three_passes(mm, orc, grid, prec):
+    """The z pass over the columns of the spectrum alone (few cells along x) and
+    over whole lines; a batchless field twice, so that columns between them
+    that the first one left behind cannot enter."""
+    banner("columns %s %s" % (grid, prec))
+    nx, ny, nz = grid
+    g = np.random.Generator(np.random.PCG64(nx + 31 * ny + nz))
+    m = g.standard_normal((2, 3, nz, ny, nx)).astype(np.float32).astype(float)
+    d = (3e-9, 2e-9, 4e-9)
+    o = orc.Oracle(grid, d, Ms=8e5, A=0.0)
+    plan = mm.Plan(grid, d, Ms=8e5, prec=prec)
+    for v in m:
+        h = to_np(plan.heff(v, None, mm.MM_DEMAG))
+        assert rel_l2(h, o.heff(v, terms=orc.DEMAG)) <= BAR[prec]
