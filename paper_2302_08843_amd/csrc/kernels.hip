@@ -671,12 +671,16 @@ __device__ __forceinline__ void adj_cell(const AdjParams& P, const T (&kz)[3], c
             T a[3] = {0, 0, 0}, l[3] = {0, 0, 0};
 #pragma unroll
             for (int n = 0; n < 6; ++n) {
+                // (a product with a zero weight would let NaN and infinities of
+                // vacuum cells in)
                 const bool ok = has[n] && msc[n + 1] != (T)0;
-                const T w = ok ? w3[n >> 1] : (T)0, iq = ok ? (T)1 / msc[n + 1] : (T)0;
+                const T w = w3[n >> 1], iq = (T)1 / msc[n + 1];
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
-                    a[c] += w * (zc[n + 1][c] * iq - z[c] * inv_ms);
-                    l[c] += w * (mc[n + 1][c] - mc[0][c]);
+                    const T dz = zc[n + 1][c] * iq - z[c] * inv_ms;
+                    const T dm = mc[n + 1][c] - mc[0][c];
+                    a[c] += w * (ok ? dz : (T)0);
+                    l[c] += w * (ok ? dm : (T)0);
                 }
             }
 #pragma unroll

@@ -340,3 +340,33 @@ def test_inverse_design_sign_pattern_on_gpu(torch_cuda, mm, orc, prec):
             assert np.sign(gy[j, i]) == (1.0 if dx < math.sqrt(2) * dy else -1.0), (i, j)
             checked += 1
     assert checked > 3000
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("grid", [(20, 6, 3), (1, 7, 5), (300, 3, 2), (40, 4, 3)])
+def test_values_in_vacuum_do_not_enter(torch_cuda, mm, prec, grid):
+    """m and w of non-magnetic cells are not part of the transposed operator:
+    with NaN and infinities there, its results at the magnetic cells are bit
+    for bit those with zeros there (demag aside, whose transform mixes every
+    cell; of the right-hand side's transpose, which starts from the field at
+    m, the Ms gradient)."""
+    banner("vjp vacuum %s %s" % (prec, grid))
+    torch = torch_cuda
+    Ms, m, w = _problem(grid, 23)
+    H = np.array([2e4, -1e4, 3e4])
+    plan = mm.Plan(grid, (3e-9, 2.5e-9, 2e-9), Ms=1.0, A=1.3e-11, Ku=3e4, alpha=0.2, prec=prec)
+    plan.set_ms(Ms)
+    terms = mm.MM_EXCH | mm.MM_ANIS | mm.MM_ZEEMAN
+    hole = Ms == 0.0
+    assert hole.any() and not hole.all()
+    out = []
+    for bad in (0.0, np.nan, np.inf):
+        mb, wb = m.copy(), w.copy()
+        mb[:, hole] = bad
+        wb[:, hole] = bad
+        out.append([*plan.heff_vjp(mb, wb, terms), plan.llg_rhs_vjp(mb, wb, H, terms)[1]])
+    mag = torch.as_tensor(~hole, device="cuda")
+    for other in out[1:]:
+        for a, b in zip(out[0], other):
+            assert torch.isfinite(a[..., mag]).all()
+            assert torch.equal(a[..., mag], b[..., mag])
