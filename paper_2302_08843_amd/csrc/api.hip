@@ -583,7 +583,8 @@ mm_status plan_build(const int grid[3], const double cell[3], double Ms, double 
     // (32 floats or 16 doubles) and therefore for the complex spectra too
     const int row_align = o.prec == MM_FP32 ? 32 : 16;
     p->Hxp = (p->Hx + row_align - 1) / row_align * row_align;
-    p->Hc = p->Hx > 1 ? (p->Hx + row_align / 2 - 1) / (row_align / 2) * (row_align / 2) : 1;
+    const int line_end = (p->Hx + row_align / 2 - 1) / (row_align / 2) * (row_align / 2);
+    p->Hc = line_end - p->Hx <= p->Hx / 8 ? line_end : p->Hx;
     p->S1n = 3L * grid[2] * grid[1] * p->Hxp;
     p->S2n = 3L * grid[2] * p->P[1] * p->Hxp;
     // layered: one kernel per unordered layer pair, nz (nz + 1) / 2 of them

@@ -51,9 +51,12 @@ struct Plan {
     double d[3];   // dx, dy, dz
     int P[3];      // padded extents
     int Hx;        // Px/2 + 1 (1 when Px == 1): x bins kept by the real transform
-    int Hc;        // columns the x, y and z passes write: Hx rounded up to 128 bytes of complex
-                   // values (partly written lines cost more: y forward 274 us against 256 at
-                   // 512x512x64 FP32)
+    int Hc;        // columns the x and y passes write (and the z pass, see launch_mid_L): Hx
+                   // rounded up to 128 bytes of complex values where that is at most an eighth
+                   // more (partly written lines cost more, y forward 274 us against 256 at
+                   // 512x512x64 FP32; a field of 33x512x40 FP64 253 against 250; but on narrow
+                   // grids the columns do: 13x400x90 127.4 with Hx, 128.6 in FP32, 172.9 and
+                   // 174.9 in FP64).  The columns from Hx on hold zeros.
     int Hxp;       // row stride of every spectral array (Hx rounded up to 128 bytes of reals)
     long N;        // cells
     long S1n;      // complex values in S1 = 3 * nz * ny * Hxp

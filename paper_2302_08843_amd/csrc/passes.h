@@ -440,10 +440,14 @@ __global__ __launch_bounds__((XR2C<T, M, TR>::kRows * XR2C<T, M, TR>::kT)) MMX_X
         const cx<T> wD = cmul(tw[k * tws], D);
         dst[k] = {S.x + wD.y, S.y - wD.x};  // S - i wD
     }
-    // the last column, and zeros up to the end of its 128 bytes
-    if (t < 128 / (int)sizeof(cx<T>) && M + t < out_row) {
-        const cx<T> Z0 = L[0];
-        dst[M + t] = {t == 0 ? Z0.x - Z0.y : (T)0, (T)0};
+    // the last column, with zeros up to the end of its 128 bytes where whole
+    // lines may follow (Plan::Hc): the y passes transform them, and what an
+    // earlier evaluation left there would grow by the padded length each time
+    constexpr int kLine = 128 / (int)sizeof(cx<T>), kPad = M >= 8 * (kLine - 1) ? kLine : 1;
+#pragma unroll
+    for (int i = t; i < kPad; i += kT) {
+        if (M + i >= out_row) break;
+        dst[M + i] = {i == 0 ? L[0].x - L[0].y : (T)0, (T)0};
     }
 }
 
@@ -1835,11 +1839,9 @@ static hipError_t launch_mid_L(const Plan& p, cx<T>* S, int n_valid, long es, lo
     const int groups = (AXIS == 2 && G > 1) ? G / 2 + 1 : G;
     const bool o32 = (size_t)p.S2n * 2 * sizeof(T) < (1ull << 32);
     const bool half = 2 * n_valid <= L && L > 1;
-    // whole lines (Hc) only where they cost no sixteenth more columns: on narrow
-    // grids the padding is up to as much again as the columns themselves
-    // (z pass with Hc and with Hx: 7 x 347 x 65 FP64 63.8 and 47.1 us,
-    // 13 x 400 x 90 FP32 59.0 and 45.9, 128 x 128 x 64 FP32 40.4 and 38.2).
-    // The columns from Hx on hold transforms that nothing reads.
+    // whole lines (Hc) only where they cost no sixteenth more columns (z pass
+    // with Hc and with Hx: 7 x 347 x 65 FP64 63.8 and 47.1 us, 13 x 400 x 90
+    // FP32 59.0 and 45.9, 128 x 128 x 64 FP32 40.4 and 38.2)
     const int ncols = p.Hc - p.Hx > p.Hx / 16 ? p.Hx : p.Hc;
     if constexpr (MMX_MIDW && MidW<T, L>::kOK) {
         using Gw = MidW<T, L>;

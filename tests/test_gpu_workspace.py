@@ -70,3 +70,21 @@ def test_workspace_rejected_when_small_or_misaligned(torch_cuda, mm):
     with pytest.raises(mm.MMError) as ei:
         mm.Plan(grid, d, Ms=8e5, prec="fp32", workspace=big, layers=[1e-9, 2e-9, 1e-9])
     assert ei.value.status == mm.MM_EINVAL
+
+
+@pytest.mark.parametrize("grid", [(7, 33, 34), (3, 9, 70), (2, 20, 65), (60, 20, 65), (130, 9, 65)])
+def test_spectrum_columns_beyond_the_last_do_not_accumulate(torch_cuda, mm, grid):
+    """Where the passes carry whole 128-byte lines of columns, those beyond the
+    last one are cleared by the x forward pass: what the workspace held there
+    is not multiplied by the padded length on every evaluation until it
+    overflows (in less than 200)."""
+    torch = torch_cuda
+    banner("spectrum columns %s" % (grid,))
+    nbytes = mm.mm_plan_workspace_bytes(grid, mm.MM_FP64)
+    ws = torch.ones((nbytes // 8,), dtype=torch.float64, device="cuda")
+    plan = mm.Plan(grid, (2e-9,) * 3, Ms=8e5, prec="fp64", workspace=ws)
+    m = plan._v(W.random_unit_sphere(grid, 5))
+    for _ in range(300):
+        h = plan.heff(m, None, mm.MM_DEMAG)
+    assert torch.isfinite(h).all()
+    assert torch.isfinite(ws).all() and ws.abs().max().item() < 1e12
