@@ -703,11 +703,17 @@ __device__ __forceinline__ void adj_cell(const AdjParams& P, const T (&kz)[3], c
 
 // nu = g + H^T z (x inverse transform of the spectrum of K z, then the
 // transposed local terms); gms += d(z.h)/dMs (double, may be null).  The
-// block shape, the wave-local transforms and the loads of cells and
-// neighbours ahead of them are those of the local pass: at 128x128x1 FP32 7.6 us
-// instead of the 19 of a version that transformed with block barriers and read
-// its neighbours one by one.  XFORM false (a single cell along x): the
-// spectrum is the field.
+// block shape and the wave-local transforms are those of the local pass: at
+// 128x128x1 FP32 7.6 us instead of the 19 of a version that transformed with
+// block barriers and read its neighbours one by one.  Small plane plans are
+// bound by latency and load cells and neighbours ahead of the transform like
+// the local pass.  Elsewhere (LATE) a thread loads one cell's after it: two
+// cells' seven neighbours of m and z held across the transform took 160 to 256
+// registers, one wave per SIMD in FP64 and spills at M = 512; now 128 at most.
+// A transposed field takes, before and with it, us: FP64 300x300x8 324 / 292,
+// 256x256x16 210 / 183, 512x512x32 1684 / 1478; FP32 512x512x1 45.2 / 41.8,
+// 300x300x8 164 / 151; kept ahead, FP64 128x64x8 35.9 / 36.8.  XFORM false (a
+// single cell along x): the spectrum is the field.
 template <typename T, int M, bool TR, bool PERCELL, bool XFORM>
 __global__ __launch_bounds__((XFORM ? XC2RW<T, M, TR>::kNT : 256)) void k_adj_local(
     const cx<T>* __restrict__ S1, const T* __restrict__ m, const T* __restrict__ z,
@@ -728,41 +734,53 @@ __global__ __launch_bounds__((XFORM ? XC2RW<T, M, TR>::kNT : 256)) void k_adj_lo
     XInvW<T, XFORM ? M : 2, TR> xi;
     if constexpr (XFORM) xi.load(S1, P.s1_comp, P.Hxp, k, j0, ny, nz, demag, tw, Lmax);
     const long N = P.N, sxy = (long)nx * ny;
-    bool cv[CPT], has[CPT][6];
-    long cell[CPT];
-    T zc[CPT][7][3], mc[CPT][7][3], msc[CPT][7], gc[CPT][3];
-    double g0[CPT];
-#pragma unroll
-    for (int q = 0; q < CPT; ++q) {
+    // slots of cells with their neighbours in registers: all of the thread's, or
+    // (LATE) one after the other
+    constexpr bool LATE = !(TR && M <= 128);
+    constexpr int NS = LATE ? 1 : CPT;
+    bool cv[NS], has[NS][6];
+    long cell[NS];
+    T zc[NS][7][3], mc[NS][7][3], msc[NS][7], gc[NS][3];
+    double g0[NS];
+    auto gather = [&](int q, int s) {
         const int li = tid + NT * q, rl = li >> LM, i = li & ((1 << LM) - 1), j = j0 + rl;
-        cv[q] = rl < RB && i < nx && j < ny;
-        const long c0 = cv[q] ? i + (long)nx * j + sxy * k : 0;
-        cell[q] = c0;
-        has[q][0] = cv[q] && i > 0;
-        has[q][1] = cv[q] && i + 1 < nx;
-        has[q][2] = cv[q] && j > 0;
-        has[q][3] = cv[q] && j + 1 < ny;
-        has[q][4] = cv[q] && k > 0;
-        has[q][5] = cv[q] && k + 1 < nz;
+        cv[s] = rl < RB && i < nx && j < ny;
+        const long c0 = cv[s] ? i + (long)nx * j + sxy * k : 0;
+        cell[s] = c0;
+        has[s][0] = cv[s] && i > 0;
+        has[s][1] = cv[s] && i + 1 < nx;
+        has[s][2] = cv[s] && j > 0;
+        has[s][3] = cv[s] && j + 1 < ny;
+        has[s][4] = cv[s] && k > 0;
+        has[s][5] = cv[s] && k + 1 < nz;
         const long off[3] = {1, nx, sxy};
 #pragma unroll
         for (int d = 0; d < 7; ++d) {
-            const long qq = d == 0 || !has[q][d - 1] ? c0 : (d & 1) ? c0 - off[(d - 1) >> 1] : c0 + off[(d - 1) >> 1];
+            const long qq = d == 0 || !has[s][d - 1] ? c0 : (d & 1) ? c0 - off[(d - 1) >> 1] : c0 + off[(d - 1) >> 1];
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                zc[q][d][c] = z[c * N + qq];
-                mc[q][d][c] = m[c * N + qq];
+                zc[s][d][c] = z[c * N + qq];
+                mc[s][d][c] = m[c * N + qq];
             }
-            msc[q][d] = PERCELL ? Ms_cell[qq] : (T)P.Ms;
+            msc[s][d] = PERCELL ? Ms_cell[qq] : (T)P.Ms;
         }
 #pragma unroll
-        for (int c = 0; c < 3; ++c) gc[q][c] = g ? g[c * N + c0] : (T)0;
-        g0[q] = gms ? gms[c0] : 0.0;
+        for (int c = 0; c < 3; ++c) gc[s][c] = g ? g[c * N + c0] : (T)0;
+        g0[s] = gms ? gms[c0] : 0.0;
+    };
+    if constexpr (!LATE) {
+#pragma unroll
+        for (int q = 0; q < CPT; ++q) gather(q, q);
     }
     if constexpr (XFORM) xi.transform(lds, twl, demag, tw, Lmax);
 #pragma unroll
     for (int q = 0; q < CPT; ++q) {
-        if (!cv[q]) continue;
+        const int s = LATE ? 0 : q;
+        if constexpr (LATE) {
+            __builtin_amdgcn_sched_barrier(0);
+            gather(q, 0);
+        }
+        if (!cv[s]) continue;
         const int li = tid + NT * q, rl = li >> LM, i = li & ((1 << LM) - 1);
         T kz[3] = {0, 0, 0}, out[3];
 #pragma unroll
@@ -774,10 +792,10 @@ __global__ __launch_bounds__((XFORM ? XC2RW<T, M, TR>::kNT : 256)) void k_adj_lo
             }
         }
         double dms;
-        adj_cell(P, kz, gc[q], zc[q], mc[q], msc[q], has[q], out, &dms);
+        adj_cell(P, kz, gc[s], zc[s], mc[s], msc[s], has[s], out, &dms);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) nu[c * N + cell[q]] = out[c];
-        if (gms) gms[cell[q]] = g0[q] + dms;
+        for (int c = 0; c < 3; ++c) nu[c * N + cell[s]] = out[c];
+        if (gms) gms[cell[s]] = g0[s] + dms;
     }
 }
 

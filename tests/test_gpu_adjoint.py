@@ -370,3 +370,23 @@ def test_values_in_vacuum_do_not_enter(torch_cuda, mm, prec, grid):
         for a, b in zip(out[0], other):
             assert torch.isfinite(a[..., mag]).all()
             assert torch.equal(a[..., mag], b[..., mag])
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("grid", [(64, 6, 2), (65, 6, 2), (129, 9, 2), (257, 6, 1), (512, 17, 2),
+                                  (300, 4, 3), (128, 3, 2), (5, 3, 3)])
+def test_transposes_by_row_length(torch_cuda, mm, orc, grid, prec):
+    """Cells and neighbours loaded before or after the x inverse transform
+    (rows of up to 128 and of more points on the transposed spectrum; always
+    after it on the other one): both transposes with all terms.  Rows of up to
+    a thousand points round a little more than VJP_TOL's grids: 1e-12 and, in
+    single precision, 4e-6."""
+    banner("transposes by row length %s %s" % (prec, grid))
+    Ms, m, w = _problem(grid, 51)
+    plan, o = _pair(mm, orc, grid, (4e-9, 3e-9, 3e-9), Ms, prec, alpha=0.1)
+    H = np.array([2e4, -1e4, 3e4])
+    o.set_field(H)
+    got = [*plan.heff_vjp(m, w, mm.MM_ALL), *plan.llg_rhs_vjp(m, w, H, mm.MM_ALL)]
+    want = [*o.heff_vjp(m, w, mm.MM_ALL & ~mm.MM_ZEEMAN), *o.llg_vjp(m, w, 0.0)]
+    for a, b in zip(got, want):
+        assert rel_l2(to_np(a), b) <= (1e-12 if prec == "fp64" else 4e-6)
