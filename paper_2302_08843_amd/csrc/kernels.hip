@@ -1001,7 +1001,9 @@ __global__ void k_fold_plane(T* __restrict__ Khat, const cx<double>* __restrict_
 // transforms the layers and rows up to the powers of two (416x314x6: 128
 // against 123).  A single layer in FP64 with rows of 1024 gains from the plane
 // kernel less than it loses in the x passes until there are many rows
-// (500x30x1: 21.4 against 20.1, 512x512x1: 46 against 64).
+// (500x30x1: 21.4 against 20.1, 512x512x1: 46 against 64).  Each line rests on
+// the one or two grids named with it; where they differ by a few per cent, so do
+// the two paths on either side of it.
 template <typename G>
 static bool plane_pays(int prec, const int n[3], const int P[3])
 {

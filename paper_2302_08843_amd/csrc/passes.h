@@ -80,7 +80,8 @@ namespace mmx {
 #ifndef MMX_RMW_F64
 #define MMX_RMW_F64 8
 #endif
-// F1 in FP32: 96 VGPRs give 5 waves per SIMD (measured -3 % at 512x512x64)
+// F1 in FP32: 96 VGPRs give 5 waves per SIMD (measured -3 % at 512x512x64), with
+// stage inputs 168 and 3 waves; with a per-cell Ms 2 to 18 registers spill there
 #ifndef MMX_XR2C_WPE_F32
 #define MMX_XR2C_WPE_F32 5
 #endif
@@ -542,16 +543,6 @@ struct Mid {
         cmin(64, cmax(1, (sizeof(T) == 4 ? MMX_MBLOCK : MMX_MBLOCK_F64) / kT));
 };
 
-// One pencil group (fixed ky for AXIS = 2) of the last-axis pass: load three
-// components, forward transform, product with the spectral kernel, inverse
-// transform, store.  HALF: n_valid <= L/2 (always true with zero padding).
-// Element (c, e) of the group is S[o + c*cs + e*es]; index arithmetic is done
-// in 32 bits when O32.  PROD 0: the symmetric demag product with the six
-// folded real components; PROD 1: the Oersted product h = j x (i g) with the
-// three folded components g (imaginary spectrum, odd along its own axis).
-// G: the thread shape (kE registers, kT threads per transform); the
-// transform's LDS scratch is lds[s * lstride].  WAVE: the kT threads of a
-// transform share one wavefront (exchanges without workgroup barriers).
 // Layout of the folded spectral kernel for the last-axis pass along an axis of
 // padded length L: [group][column tile][NK components][L/2+1][KW columns]
 // (group ky when the pass runs along z, one group when it runs along y), so
@@ -590,6 +581,16 @@ struct KGlobal {
     }
 };
 
+// One pencil group (fixed ky for AXIS = 2) of the last-axis pass: load three
+// components, forward transform, product with the spectral kernel, inverse
+// transform, store.  HALF: n_valid <= L/2 (always true with zero padding).
+// Element (c, e) of the group is S[o + c*cs + e*es]; index arithmetic is done
+// in 32 bits when O32.  PROD 0: the symmetric demag product with the six
+// folded real components; PROD 1: the Oersted product h = j x (i g) with the
+// three folded components g (imaginary spectrum, odd along its own axis).
+// G: the thread shape (kE registers, kT threads per transform); the
+// transform's LDS scratch is lds[s * lstride].  WAVE: the kT threads of a
+// transform share one wavefront (exchanges without workgroup barriers).
 // KG: the kernel accessor kget(c, kyf, kzf) (c = component, kyf/kzf the
 // folded y and z indices; the sign flips are applied here).
 // Load the three components of one column of the group: v[c][r] = element
@@ -698,7 +699,7 @@ __device__ __forceinline__ void mid_group(cx<T> (&v)[3][G::kE], cx<T>* S, long o
 // spectral kernel.  ADJ: the two groups go to adjacent blocks instead (same
 // XCD, same time), so the second read of each kernel row is an L2 hit rather
 // than a re-read after the rows have left L2.  AXIS = 1: pencils along y
-// (single layer), one group.  O32: spectra and kernel arrays below 4 GiB.
+// (single layer), one group.  O32: spectra below 4 GiB.
 template <typename T, int L, int AXIS, bool HALF, bool O32, bool ADJ, int PROD = 0>
 __global__ __launch_bounds__((Mid<T, L>::kB * Mid<T, L>::kT)) void k_mid(
     cx<T>* S, const T* __restrict__ Khat, int n_valid, long es, long cs, long gstride, int ncols,

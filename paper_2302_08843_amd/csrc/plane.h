@@ -91,14 +91,17 @@ __host__ __device__ inline int plane_kn(int q, int YP) { return YP / 2 + (q ? 0 
 // 256x256x16 107 / 91, 512x256x16 190 / 167; FP64 32x32x4 25.1 / 18.0,
 // 256x256x4 61.4 / 50.5, 256x256x8 92.3 / 80.1.  Single layers, whose z pass
 // along y held 8 columns in one wavefront for 12 us at any small size: FP32
-// 64x64x1 21.0 / 15.0, 512x512x1 52.9 / 31.6; FP64 19.8 / 16.5, 63.7 / 45.6.  It is bound by VALU issue and
-// by the latency of its phases (a plane of 104 KB leaves one block per compute
-// unit, whose wavefronts meet at every barrier; VALUs busy about half of the
-// time), not by memory.  Hence as many threads as fit 128 registers without
-// spills (256x256x8: 1024 threads 48.3, 512 threads 52.2; a version that
-// spilled 50 registers took 100x500x3 from 41 to 65), no branches inside the
-// phases (layers beyond nz are rows of zeros), and a spectrum with y fastest
-// (reading columns of the row-major one: 256x256x8 81).
+// 64x64x1 21.0 / 15.0, 512x512x1 52.9 / 31.6; FP64 19.8 / 16.5, 63.7 / 45.6.
+// It is bound by VALU issue and by the latency of its phases (a plane of 104 KB
+// leaves one block per compute unit, whose wavefronts meet at every barrier;
+// VALUs busy about half of the time), not by memory.  Hence as many threads as fit 128 registers, where that
+// takes few spills (256x256x8: 1024 threads 48.3, 512 threads 52.2; a version
+// that spilled 50 registers took 100x500x3 from 41 to 65): all shapes fit but
+// the two of 1024 threads in FP32 that run one q after the other, (256, 32)
+// with 23 registers spilled, the one of 256x256x16 above, and (512, 16) with
+// 47.  No branches inside the phases (layers beyond nz are rows of zeros), and
+// a spectrum with y fastest (reading columns of the row-major one: 256x256x8
+// 81).
 template <typename T, int YP, int EY, int PZ, int LZ, int NQ, int NTQ>
 __global__ __launch_bounds__((PlaneG<T, YP, EY, PZ, LZ, NQ, NTQ>::kNT)) void k_plane(
     cx<T>* __restrict__ ST, cx<T>* __restrict__ scratch, const T* __restrict__ KT, int ny, int nz,
