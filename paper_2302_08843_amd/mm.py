@@ -795,7 +795,8 @@ class RegionLoss:
 
     def __init__(self, plan, m0, dt, nsteps, region, h_ext=None, terms=MM_ALL, t0=0.0,
                  ckpt_every=50):
-        self.plan, self.m0 = plan, plan._v(m0)
+        # (an own tensor on m0's storage: _v may return m0 itself)
+        self.plan, self.m0 = plan, plan._v(m0).view(plan.shape)
         self.dt, self.nsteps, self.region = float(dt), int(nsteps), plan._region(region)
         self.h_ext, self.terms, self.t0, self.every = h_ext, terms, float(t0), int(ckpt_every)
 

@@ -197,3 +197,25 @@ def test_workspace_size_query():
     assert mm.mm_plan_workspace_bytes((4, 4, 4), 7) == 0
     # the large benchmark grid: kernel 410.5 MB + spectra 1.22 GB + RK 2.01 GB (FP32)
     assert abs(mm.mm_plan_workspace_bytes((512, 512, 64), mm.MM_FP32) / 1e9 - 3.70) < 0.05
+
+
+def test_region_loss_keeps_its_start_state():
+    """RegionLoss holds the start state's storage, not the caller's tensor
+    object: a parameter whose .data is replaced later (moved to another device
+    or precision with its module) leaves the loss as it was set up."""
+    import types
+
+    import torch
+
+    from paper_2302_08843_amd import mm
+
+    plan = types.SimpleNamespace(shape=(3, 2, 4, 5), dtype=torch.float64,
+                                 device=torch.device("cpu"), _region=lambda r: r)
+    plan._t = types.MethodType(mm.Plan._t, plan)
+    plan._v = types.MethodType(mm.Plan._v, plan)
+    m0 = torch.nn.Parameter(torch.randn(plan.shape, dtype=torch.float64))
+    kept = m0.detach()
+    loss = mm.RegionLoss(plan, m0, 1e-13, 4, None)
+    assert loss.m0.data_ptr() == kept.data_ptr()
+    m0.data = torch.zeros(plan.shape, dtype=torch.float32)
+    assert loss.m0.dtype == torch.float64 and torch.equal(loss.m0, kept)
